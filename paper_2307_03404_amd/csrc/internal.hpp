@@ -72,6 +72,18 @@ hipError_t launch_fused(const KGrid& g, const KRays& rs, const KOpts& op, const 
                         int64_t* stats, unsigned* ws, int block, int variant,
                         unsigned long long* gfix, hipStream_t st);
 
+// A team of 2^log_t lanes per ray (team.hip).  team_lanes_log2 says how many for a
+// batch of n_rays and the gradients wanted (1: grid, 2: pose); 0 = one lane per ray.
+int team_lanes_log2(int64_t n_rays, int want);
+hipError_t team_forward(const KGrid& g, const KRays& rs, const KOpts& op, int log_t, float* rgb, float* depth,
+                        int32_t* nsamp, hipStream_t st);
+hipError_t team_backward(const KGrid& g, const KRays& rs, const KOpts& op, int log_t, const float* rgb,
+                         const float* depth, const int32_t* nsamp, const float* g_rgb, const float* g_depth,
+                         float* grad_data, double* grad_pose, hipStream_t st);
+hipError_t team_fused(const KGrid& g, const KRays& rs, const KOpts& op, int log_t, const float* tgt_rgb,
+                      const float* tgt_depth, const float* frame_weight, int want, float* rgb, float* depth,
+                      double* loss, float* grad_data, double* grad_pose, hipStream_t st);
+
 // set: grad_data = dTV for the visited records' used fields, else += dTV
 hipError_t launch_tv(const KGrid& g, float lambda_density, float lambda_sh, float eps,
                      float* grad_data, bool set, hipStream_t st);

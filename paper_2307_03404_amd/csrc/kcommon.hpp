@@ -548,4 +548,29 @@ __device__ __forceinline__ void gather_interp(const KGrid& g, const int idx[8], 
     }
 }
 
+// ---------------------------------------------------------------------------
+// pose gradient of one ray
+// ---------------------------------------------------------------------------
+
+struct PoseAcc {
+    float go[3];        // dL/do summed over samples (Eq. 14: dp/do = 1)
+    float gd[3];        // dL/dd through positions (dp/dd = t_i)
+    float gv[3];        // dL/dd through the SH basis (optional exact term)
+};
+
+// (g_rho, g_phi) of one ray: rho = g_o, phi = o x g_o + d x g_d (+ d x g_view).
+template <bool VIEW>
+__device__ __forceinline__ void pose_six(const Ray& ray, const PoseAcc& pa, double out[6]) {
+    const float* o = ray.o;
+    const float* d = ray.d;
+    float gd[3] = {pa.gd[0], pa.gd[1], pa.gd[2]};
+    if (VIEW) { gd[0] += pa.gv[0]; gd[1] += pa.gv[1]; gd[2] += pa.gv[2]; }
+    out[0] = pa.go[0];
+    out[1] = pa.go[1];
+    out[2] = pa.go[2];
+    out[3] = (double)(o[1] * pa.go[2] - o[2] * pa.go[1]) + (double)(d[1] * gd[2] - d[2] * gd[1]);
+    out[4] = (double)(o[2] * pa.go[0] - o[0] * pa.go[2]) + (double)(d[2] * gd[0] - d[0] * gd[2]);
+    out[5] = (double)(o[0] * pa.go[1] - o[1] * pa.go[0]) + (double)(d[0] * gd[1] - d[1] * gd[0]);
+}
+
 }  // namespace pxm

@@ -1,5 +1,6 @@
-// Forward, backward, fused and Gauss-Newton kernels of the sparse-voxel volume
-// renderer.
+// Forward, backward and fused kernels of the sparse-voxel volume renderer with
+// one lane per ray: the form for batches that fill the card, and of the
+// launch tunings 1 and 2 (team.hip holds the others).
 //
 // One lane per ray.  A wave holds 64 rays of one pixel tile (the ray packer
 // orders full frames in 8x8 tiles), so the lanes gather nearly the same
@@ -9,9 +10,7 @@
 // cells (exact: they interpolate to zero density) and composite colour and
 // range.  Backward (Eq. 6-14): replay exactly the
 // forward's nsamp positions, re-deriving sigma, c, w and T_{i+1} (nothing is
-// stored per sample), and scatter or reduce the gradients.  Gauss-Newton
-// (Sec. 5.3): per-ray pose Jacobians of the four outputs from the same march,
-// reduced to per-frame normal equations.
+// stored per sample), and scatter or reduce the gradients.
 #include <atomic>
 #include <type_traits>
 
@@ -134,12 +133,6 @@ __device__ __forceinline__ void ray_forward(const KGrid& g, const KOpts& op, con
     out.occ_corners = occc;
     out.grad_corners = gradc;
 }
-
-struct PoseAcc {
-    float go[3];        // dL/do summed over samples (Eq. 14: dp/do = 1)
-    float gd[3];        // dL/dd through positions (dp/dd = t_i)
-    float gv[3];        // dL/dd through the SH basis (optional exact term)
-};
 
 // Running state of a backward march.
 struct BwdState {
@@ -362,142 +355,6 @@ __device__ __forceinline__ void ray_backward(const KGrid& g, const KOpts& op, co
     }
 }
 
-// (g_rho, g_phi) of one ray: rho = g_o, phi = o x g_o + d x g_d (+ d x g_view).
-template <bool VIEW>
-__device__ __forceinline__ void pose_six(const Ray& ray, const PoseAcc& pa, double out[6]) {
-    const float* o = ray.o;
-    const float* d = ray.d;
-    float gd[3] = {pa.gd[0], pa.gd[1], pa.gd[2]};
-    if (VIEW) { gd[0] += pa.gv[0]; gd[1] += pa.gv[1]; gd[2] += pa.gv[2]; }
-    out[0] = pa.go[0];
-    out[1] = pa.go[1];
-    out[2] = pa.go[2];
-    out[3] = (double)(o[1] * pa.go[2] - o[2] * pa.go[1]) + (double)(d[1] * gd[2] - d[2] * gd[1]);
-    out[4] = (double)(o[2] * pa.go[0] - o[0] * pa.go[2]) + (double)(d[2] * gd[0] - d[0] * gd[2]);
-    out[5] = (double)(o[0] * pa.go[1] - o[1] * pa.go[0]) + (double)(d[0] * gd[1] - d[1] * gd[0]);
-}
-
-// ---------------------------------------------------------------------------
-// Gauss-Newton tracking: per-ray pose Jacobian of (R, G, B, z-depth)
-// ---------------------------------------------------------------------------
-
-// Pose accumulators of the four outputs (colour channels, then z-depth).
-struct JacAcc {
-    float go[4][3];
-    float gd[4][3];
-    float gv[4][3];
-};
-
-// One occupied sample of the Jacobian march: row k is the pose gradient of
-// output k alone (unit upstream on it), so the sample's factors are those of
-// Eq. 8-10 with gC = e_k (colour rows) or dL/d range = 1/s (depth row).
-template <bool VIEW, int DEG>
-__device__ __forceinline__ void jacobian_sample(const KGrid& g, const KOpts& op, const Ray& ray,
-                                                const float Y[9], const float GY[9][3],
-                                                const Sample& s, const double Chat[3], double Dhat,
-                                                BwdState& st, JacAcc& ja) {
-    int idx[8];
-    if (load_links(g, s.base, idx) == 0) return;
-    Interp v;
-    gather_interp<true, VIEW, DEG>(g, idx, Y, GY, s.f, v);
-    const float sr = v.sig;
-    if (!(sr > 0.f)) return;
-    const float delta = op.step_vox;
-    const float x = sr * delta;
-    const float wt = st.T * (-expm1f(-x));
-    st.L += (double)x;
-    const float Tn = trans_of(st.L);
-    float c[3], dact[3];
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-        c[ch] = act_fwd(op.act, v.s[ch]);
-        dact[ch] = act_bwd(op.act, v.s[ch]) * wt;
-        st.A[ch] = fma((double)wt, (double)c[ch], st.A[ch]);
-    }
-    st.AD = fma((double)wt, (double)s.t, st.AD);
-    // per-output density factor (Eq. 9 / Eq. 10) and colour factor (Eq. 8)
-    float gsig[4];
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) gsig[ch] = delta * (c[ch] * Tn + (float)(st.A[ch] - Chat[ch]));
-    gsig[3] = delta * (s.t * Tn + (float)(st.AD - Dhat)) / ray.s;
-    const float inv_vs = (float)g.inv_vs;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            float gp = gsig[k] * v.dsig[a];
-            if (k < 3) gp = fmaf(dact[k < 3 ? k : 0], v.ds[k < 3 ? k : 0][a], gp);
-            gp *= inv_vs;
-            ja.go[k][a] += gp;
-            ja.gd[k][a] = fmaf(s.t, gp, ja.gd[k][a]);
-            if (VIEW && k < 3) ja.gv[k][a] = fmaf(dact[k < 3 ? k : 0], v.ev[k < 3 ? k : 0][a], ja.gv[k][a]);
-        }
-    }
-    st.T = Tn;
-}
-
-// Jacobian rows J[k] = (g_o, o x g_o + d x g_d (+ d x g_view)) of one ray.
-template <bool VIEW, int DEG>
-__device__ __forceinline__ void ray_jacobian(const KGrid& g, const KOpts& op, const Ray& ray,
-                                             const float Y[9], int n, const double Chat[3],
-                                             double Dhat, float J[4][6],
-                                             const uint32_t* marks = nullptr, int mark_last = 0,
-                                             bool mark_overflow = true) {
-    float GY[9][3];
-    if (VIEW) sh9_grad(ray.d[0], ray.d[1], ray.d[2], GY);
-    BwdState st = {{0.0, 0.0, 0.0}, 0.0, 1.f, 0.0};
-    JacAcc ja;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) ja.go[k][a] = ja.gd[k][a] = ja.gv[k][a] = 0.f;
-    const int64_t ke = ray.k_first + (n > 0 ? n : 0);
-    if (marks && !mark_overflow) {
-        for (int off = n > 0 ? next_mark(marks, mark_last, 0) : -1; off >= 0;
-             off = next_mark(marks, mark_last, off + 1)) {
-            Sample s;
-            if (!sample_at(g, ray, ray.k_first + off, s)) break;
-            jacobian_sample<VIEW, DEG>(g, op, ray, Y, GY, s, Chat, Dhat, st, ja);
-        }
-    } else {
-        int64_t k = ray.k_first;
-        OccCache oc;
-        occ_cache_init(oc);
-        while (k < ke) {
-            Sample s;
-            if (!sample_at(g, ray, k, s)) break;
-            if (g.occ0) {
-                int64_t nxt;
-                const int cls = occ_classify(g, ray, k, s.c, oc, nxt);
-                if (cls == OCC_JUMP) {
-                    k = nxt < ke ? nxt : ke;
-                    continue;
-                }
-                if (cls == OCC_EMPTY_CELL) {
-                    ++k;
-                    continue;
-                }
-            }
-            jacobian_sample<VIEW, DEG>(g, op, ray, Y, GY, s, Chat, Dhat, st, ja);
-            ++k;
-        }
-    }
-    const float* o = ray.o;
-    const float* d = ray.d;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        float gd[3] = {ja.gd[q][0], ja.gd[q][1], ja.gd[q][2]};
-        if (VIEW) { gd[0] += ja.gv[q][0]; gd[1] += ja.gv[q][1]; gd[2] += ja.gv[q][2]; }
-        const float* go = ja.go[q];
-        J[q][0] = go[0];
-        J[q][1] = go[1];
-        J[q][2] = go[2];
-        J[q][3] = (o[1] * go[2] - o[2] * go[1]) + (d[1] * gd[2] - d[2] * gd[1]);
-        J[q][4] = (o[2] * go[0] - o[0] * go[2]) + (d[2] * gd[0] - d[0] * gd[2]);
-        J[q][5] = (o[0] * go[1] - o[1] * go[0]) + (d[0] * gd[1] - d[1] * gd[0]);
-    }
-}
-
 // ---------------------------------------------------------------------------
 // kernels
 // ---------------------------------------------------------------------------
@@ -521,21 +378,18 @@ __global__ void __launch_bounds__(256) k_forward(KGrid g, KRays rs, KOpts op, fl
     nsamp[r] = fr.n;
 }
 
-template <bool GRID, bool POSE, bool VIEW, int DEG>
+template <int DEG>
 __global__ void __launch_bounds__(256) k_backward(KGrid g, KRays rs, KOpts op,
                                                   const float* __restrict__ rgb,
                                                   const float* __restrict__ depth,
                                                   const int32_t* __restrict__ nsamp,
                                                   const float* __restrict__ g_rgb,
                                                   const float* __restrict__ g_depth,
-                                                  float* __restrict__ grad,
-                                                  double* __restrict__ grad_pose) {
+                                                  float* __restrict__ grad) {
     extern __shared__ float smem[];
-    WaveStage wc{nullptr, nullptr, nullptr, nullptr};
-    if (GRID) wc = wave_stage(smem);
+    const WaveStage wc = wave_stage(smem);
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool active = r < rs.n;
-    int f = 0;
     Ray ray;
     PoseAcc pa = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
     float Y[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -552,8 +406,7 @@ __global__ void __launch_bounds__(256) k_backward(KGrid g, KRays rs, KOpts op,
         const float gD = g_depth[r];
         active = gC[0] != 0.f || gC[1] != 0.f || gC[2] != 0.f || gD != 0.f;
         if (active) {
-            f = frame_of(rs.off, rs.F, r);
-            setup_ray(g, rs, op, r, f, ray);
+            setup_ray(g, rs, op, r, frame_of(rs.off, rs.F, r), ray);
             sh9(ray.d[0], ray.d[1], ray.d[2], Y);
             Chat[0] = rgb[3 * r];
             Chat[1] = rgb[3 * r + 1];
@@ -563,12 +416,7 @@ __global__ void __launch_bounds__(256) k_backward(KGrid g, KRays rs, KOpts op,
             n = ray.empty ? 0 : nsamp[r];
         }
     }
-    ray_backward<GRID, POSE, VIEW, DEG>(g, op, ray, Y, n, Chat, Dhat, gC, gDr, grad, wc, pa);
-    if (POSE) {
-        double six[6] = {0, 0, 0, 0, 0, 0};
-        if (active) pose_six<VIEW>(ray, pa, six);
-        seg_sum_atomic<6>(f, active, six, grad_pose);
-    }
+    ray_backward<true, false, false, DEG>(g, op, ray, Y, n, Chat, Dhat, gC, gDr, grad, wc, pa);
 }
 
 // Fused step, in one launch (PH 0) or split in two (PH 1: forward and loss,
@@ -732,68 +580,6 @@ __global__ void __launch_bounds__(256, (PH == 1 ? 4 : 1)) k_fused(KGrid g, KRays
     }
 }
 
-// Gauss-Newton normal equations: per ray, forward, 4-residual and Jacobian;
-// per frame, H = sum w J^T W J (upper triangle), g = sum w J^T W e and the
-// error E, with W = diag(1, 1, 1, lambda_depth) over rays with a valid depth.
-template <bool VIEW, int DEG>
-__global__ void __launch_bounds__(256) k_gn(KGrid g, KRays rs, KOpts op,
-                                            const float* __restrict__ tgt_rgb,
-                                            const float* __restrict__ tgt_depth,
-                                            const float* __restrict__ fw,
-                                            double* __restrict__ gn) {
-    extern __shared__ uint32_t gn_marks[];
-    uint32_t* marks = gn_marks + (threadIdx.x / WAVE) * (MARK_WORDS * WAVE) + lane_id();
-    const int64_t r = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    const bool inr = r < rs.n;
-    int f = 0;
-    bool valid = false;
-    double vals[GN_VALUES];
-#pragma unroll
-    for (int i = 0; i < GN_VALUES; ++i) vals[i] = 0.0;
-    if (inr) {
-        f = frame_of(rs.off, rs.F, r);
-        Ray ray;
-        setup_ray(g, rs, op, r, f, ray);
-        float Y[9];
-        sh9(ray.d[0], ray.d[1], ray.d[2], Y);
-        FwdResult fr;
-        ray_forward<DEG>(g, op, ray, Y, fr, marks);
-        const float Dt = tgt_depth[r];
-        valid = isfinite(Dt) && Dt > 0.f;
-        if (valid) {
-            const float e[4] = {fr.C[0] - tgt_rgb[3 * r], fr.C[1] - tgt_rgb[3 * r + 1],
-                                fr.C[2] - tgt_rgb[3 * r + 2], fr.D / ray.s - Dt};
-            float J[4][6];
-            ray_jacobian<VIEW, DEG>(g, op, ray, Y, fr.n, fr.Cd, fr.Dd, J, marks, fr.mark_last,
-                               fr.mark_overflow);
-            const double wf = (double)fw[f];
-            const double Wk[4] = {wf, wf, wf, wf * (double)op.lambda_d};
-            int q = 0;
-#pragma unroll
-            for (int i = 0; i < 6; ++i)
-#pragma unroll
-                for (int j = i; j < 6; ++j) {
-                    double acc = 0.0;
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) acc += Wk[k] * (double)J[k][i] * (double)J[k][j];
-                    vals[q++] = acc;
-                }
-#pragma unroll
-            for (int i = 0; i < 6; ++i) {
-                double acc = 0.0;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) acc += Wk[k] * (double)J[k][i] * (double)e[k];
-                vals[21 + i] = acc;
-            }
-            double E = 0.0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) E += Wk[k] * (double)e[k] * (double)e[k];
-            vals[27] = E;
-        }
-    }
-    seg_sum_atomic<GN_VALUES>(f, valid, vals, gn);
-}
-
 // Deterministic scatter, last step: grad += fixed-point sum x 2^-FIX_SHIFT
 // (one conversion of an exact integer sum), and the buffer is zeroed for the
 // next call.  Padding fields of a record are left alone.
@@ -826,6 +612,8 @@ static void by_degree(int deg, F&& f) {
 
 hipError_t launch_forward(const KGrid& g, const KRays& rs, const KOpts& op, float* rgb,
                           float* depth, int32_t* nsamp, hipStream_t st) {
+    const int lt = team_lanes_log2(rs.n, 0);
+    if (lt > 0) return team_forward(g, rs, op, lt, rgb, depth, nsamp, st);
     by_degree(g.deg, [&](auto D) {
         hipLaunchKernelGGL(k_forward<decltype(D)::value>, dim3(blocks_for(rs.n, 256)), dim3(256), 0, st,
                            g, rs, op, rgb, depth, nsamp);
@@ -837,24 +625,15 @@ hipError_t launch_backward(const KGrid& g, const KRays& rs, const KOpts& op, con
                            const float* depth, const int32_t* nsamp, const float* g_rgb,
                            const float* g_depth, float* grad_data, double* grad_pose,
                            hipStream_t st) {
-    const dim3 grid(blocks_for(rs.n, 256)), block(256);
-    const bool view = (op.flags & 1) != 0;
     if (!((grad_data != nullptr) ^ (grad_pose != nullptr))) return hipErrorInvalidValue;
+    // the pose gradient has no one-lane form of its own: a team of one is faster
+    const int lt = team_lanes_log2(rs.n, grad_data ? 1 : 2);
+    if (lt > 0 || grad_pose)
+        return team_backward(g, rs, op, lt, rgb, depth, nsamp, g_rgb, g_depth, grad_data, grad_pose, st);
     by_degree(g.deg, [&](auto D) {
-        constexpr int DEG = decltype(D)::value;
-        if (grad_data) {
-            // one wave per workgroup: each wave stages its MFMA operands in ~19 KB of LDS
-            const size_t lds = WAVE_LDS_FLOATS * sizeof(float);
-            hipLaunchKernelGGL((k_backward<true, false, false, DEG>), dim3(blocks_for(rs.n, WAVE)),
-                               dim3(WAVE), lds, st, g, rs, op, rgb, depth, nsamp, g_rgb, g_depth,
-                               grad_data, grad_pose);
-        } else if (view) {
-            hipLaunchKernelGGL((k_backward<false, true, true, DEG>), grid, block, 0, st, g, rs, op, rgb,
-                               depth, nsamp, g_rgb, g_depth, grad_data, grad_pose);
-        } else {
-            hipLaunchKernelGGL((k_backward<false, true, false, DEG>), grid, block, 0, st, g, rs, op, rgb,
-                               depth, nsamp, g_rgb, g_depth, grad_data, grad_pose);
-        }
+        // one wave per workgroup: each wave stages its MFMA operands in ~19 KB of LDS
+        hipLaunchKernelGGL((k_backward<decltype(D)::value>), dim3(blocks_for(rs.n, WAVE)), dim3(WAVE),
+                           WAVE_LDS_FLOATS * sizeof(float), st, g, rs, op, rgb, depth, nsamp, g_rgb, g_depth, grad_data);
     });
     return hipGetLastError();
 }
@@ -938,6 +717,12 @@ hipError_t launch_fused(const KGrid& g, const KRays& rs, const KOpts& op, const 
                         float* depth, double* loss, float* grad_data, double* grad_pose,
                         int64_t* stats, unsigned* ws, int block, int variant,
                         unsigned long long* gfix, hipStream_t st) {
+    // variant 0 takes a team of lanes per ray where that is faster (team_lanes_log2;
+    // for the pose alone at every size); the counters and the fixed-point
+    // scatter, whose result does not depend on the launch form, stay with one
+    const int lt = team_lanes_log2(rs.n, want);
+    if (variant == 0 && !gfix && !(want & 4) && (lt > 0 || (want & 3) == 2))
+        return team_fused(g, rs, op, lt, tgt_rgb, tgt_depth, frame_weight, want, rgb, depth, loss, grad_data, grad_pose, st);
     if (want & 1) {
         // the grid scatter needs WAVE_LDS_FLOATS of LDS per wave: shrink the
         // workgroup if the device cannot give this many waves' worth
@@ -978,22 +763,6 @@ hipError_t launch_fused(const KGrid& g, const KRays& rs, const KOpts& op, const 
         hipLaunchKernelGGL(k_fix_finalize, dim3((unsigned)(wgs < (1 << 20) ? wgs : (1 << 20))), dim3(256), 0,
                            st, gfix, grad_data, n, S, 1 + 3 * (g.deg + 1) * (g.deg + 1));
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_gn(const KGrid& g, const KRays& rs, const KOpts& op, const float* tgt_rgb,
-                     const float* tgt_depth, const float* frame_weight, double* gn, hipStream_t st) {
-    const dim3 grid(blocks_for(rs.n, 256)), block(256);
-    const size_t lds = (256 / WAVE) * MARK_WORDS * WAVE * sizeof(uint32_t);
-    by_degree(g.deg, [&](auto D) {
-        constexpr int DEG = decltype(D)::value;
-        if (op.flags & 1)
-            hipLaunchKernelGGL((k_gn<true, DEG>), grid, block, lds, st, g, rs, op, tgt_rgb, tgt_depth,
-                               frame_weight, gn);
-        else
-            hipLaunchKernelGGL((k_gn<false, DEG>), grid, block, lds, st, g, rs, op, tgt_rgb, tgt_depth,
-                               frame_weight, gn);
-    });
     return hipGetLastError();
 }
 
