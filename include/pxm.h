@@ -405,10 +405,11 @@ size_t pxm_workspace_bytes(const pxm_grid *grid, const pxm_rays *rays, const pxm
 
 /*
  * Launch tuning for pxm_render_fused (process-wide; read at each call):
- *   block    rays per workgroup (64, 128 or 256; 0 = default 256)
- *   variant  0 = plain launches: one workgroup per ray tile, and for the pose
+ *   block    rays per workgroup of variants 1 and 2 (64, 128 or 256; 0 =
+ *            default 256)
+ *   variant  0 = plain launches: one wave per tile of 64 rays, and for the pose
  *            alone, or where a batch is too small to fill the card with one
- *            lane per ray, a team of lanes per ray (block is not used then),
+ *            lane per ray, a team of lanes per ray,
  *            1 = persistent workgroups
  *            pulling ray tiles from a device counter in the workspace,
  *            2 = two persistent launches: the forward and loss (few

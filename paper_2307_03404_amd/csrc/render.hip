@@ -359,10 +359,15 @@ __device__ __forceinline__ void ray_backward(const KGrid& g, const KOpts& op, co
 // kernels
 // ---------------------------------------------------------------------------
 
+// Rays per workgroup of the forward kernel: one wave, which leaves its registers
+// as soon as its own rays end (64 sparse frames of the 512^3 room 7.15 ms with
+// four waves, 6.56 with one; the 1200x680 room frame 370 -> 351 us).
+constexpr int FORWARD_RAYS = WAVE;
+
 template <int DEG>
-__global__ void __launch_bounds__(256) k_forward(KGrid g, KRays rs, KOpts op, float* __restrict__ rgb,
+__global__ void __launch_bounds__(FORWARD_RAYS) k_forward(KGrid g, KRays rs, KOpts op, float* __restrict__ rgb,
                                                  float* __restrict__ depth, int32_t* __restrict__ nsamp) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t r = ray_tile(blockIdx.x, gridDim.x) * FORWARD_RAYS + threadIdx.x;
     if (r >= rs.n) return;
     const int f = frame_of(rs.off, rs.F, r);
     Ray ray;
@@ -379,7 +384,7 @@ __global__ void __launch_bounds__(256) k_forward(KGrid g, KRays rs, KOpts op, fl
 }
 
 template <int DEG>
-__global__ void __launch_bounds__(256) k_backward(KGrid g, KRays rs, KOpts op,
+__global__ void __launch_bounds__(WAVE) k_backward(KGrid g, KRays rs, KOpts op,
                                                   const float* __restrict__ rgb,
                                                   const float* __restrict__ depth,
                                                   const int32_t* __restrict__ nsamp,
@@ -388,7 +393,7 @@ __global__ void __launch_bounds__(256) k_backward(KGrid g, KRays rs, KOpts op,
                                                   float* __restrict__ grad) {
     extern __shared__ float smem[];
     const WaveStage wc = wave_stage(smem);
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t r = ray_tile(blockIdx.x, gridDim.x) * WAVE + threadIdx.x;
     bool active = r < rs.n;
     Ray ray;
     PoseAcc pa = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
@@ -456,7 +461,7 @@ __global__ void __launch_bounds__(256, (PH == 1 ? 4 : 1)) k_fused(KGrid g, KRays
             __syncthreads();
             if (tile >= n_tiles) break;
         } else {
-            tile = xcd_tile(blockIdx.x, gridDim.x);
+            tile = ray_tile(blockIdx.x, gridDim.x);
         }
         const int64_t r = tile * blockDim.x + threadIdx.x;
         const bool inr = r < rs.n;
@@ -615,8 +620,8 @@ hipError_t launch_forward(const KGrid& g, const KRays& rs, const KOpts& op, floa
     const int lt = team_lanes_log2(rs.n, 0);
     if (lt > 0) return team_forward(g, rs, op, lt, rgb, depth, nsamp, st);
     by_degree(g.deg, [&](auto D) {
-        hipLaunchKernelGGL(k_forward<decltype(D)::value>, dim3(blocks_for(rs.n, 256)), dim3(256), 0, st,
-                           g, rs, op, rgb, depth, nsamp);
+        hipLaunchKernelGGL(k_forward<decltype(D)::value>, dim3(blocks_for(rs.n, FORWARD_RAYS)), dim3(FORWARD_RAYS),
+                           0, st, g, rs, op, rgb, depth, nsamp);
     });
     return hipGetLastError();
 }
@@ -723,6 +728,10 @@ hipError_t launch_fused(const KGrid& g, const KRays& rs, const KOpts& op, const 
     const int lt = team_lanes_log2(rs.n, want);
     if (variant == 0 && !gfix && !(want & 4) && (lt > 0 || (want & 3) == 2))
         return team_fused(g, rs, op, lt, tgt_rgb, tgt_depth, frame_weight, want, rgb, depth, loss, grad_data, grad_pose, st);
+    // a wave works alone: workgroups of one wave leave no registers and LDS with
+    // waves that wait for the slowest of four (64 uneven frames of the 512^3
+    // room 35.0 ms with 256 rays per workgroup, 31.6 with 64)
+    if (variant == 0) block = WAVE;
     if (want & 1) {
         // the grid scatter needs WAVE_LDS_FLOATS of LDS per wave: shrink the
         // workgroup if the device cannot give this many waves' worth

@@ -349,7 +349,7 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
     tm.sub = lane & (tm.T - 1);
     tm.base = lane - tm.sub;
     tm.mask = (tm.T == WAVE ? ~0ull : (1ull << tm.T) - 1ull) << tm.base;
-    const int64_t r = (xcd_tile(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> log_t;
+    const int64_t r = (ray_tile(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> log_t;
     const bool inr = r < rs.n;
     int f = 0;
     Ray ray;
