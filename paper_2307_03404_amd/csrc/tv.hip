@@ -8,26 +8,25 @@
 //                           + dx(v-x)/root(v-x)                    if v-x has a term
 //                           + dy(v-y)/root(v-y) + dz(v-z)/root(v-z)  (likewise) ]
 //
-// Blocks of 8^3 lattice vertices, one workgroup each, split into eight 4^3
-// sub-bricks.  The workgroup tests the block against the occupancy bitfield
-// once, loads the links of the block and its one-vertex halo (10^3) in one
-// pass, and then, for each sub-brick with an allocated vertex, stages the
-// sub-brick's 6^3 halo records with all their fields at once (each record
-// read as one contiguous run: 112 bytes at SH degree 2, and kept in LDS
-// position-major, as it arrived) and computes its
-// vertices' fields (28 at degree 2, 13 at degree 1, 4 at degree 0) with
-// consecutive lanes, so each gradient record is written as one run.
-// (Staging four fields at a time over 8^3 blocks fetched every record line
-// once per chunk, as the lines of ~200 blocks in flight per XCD do not
-// survive in L2 between chunks; one workgroup per 4^3 brick made the launch
-// dispatch-bound on sparse 512^3 grids.)  Blocks are dealt to XCDs in
-// contiguous runs so that halos shared with neighbours are read through the
-// same L2.  Each phase issues all of a thread's global loads before it uses
-// any (links, staged records, gradient entries), so a phase costs one memory
-// round trip: the gradient read-modify-writes, one per item in turn, were the
-// longest chain.  The allocated vertices of all eight sub-bricks are listed
-// first, so that the records of the next non-empty sub-brick are requested
-// before the current one is computed and arrive while it is.
+// Blocks of 8^3 lattice vertices, one workgroup each.  The workgroup tests the
+// block against the occupancy bitfield, loads the links of the block and its
+// one-vertex halo (10^3) into LDS in one pass and lists its allocated vertices
+// with the terms that touch each.  Then Q lanes per vertex (7 at SH degree 2)
+// each take one float4 of its record: they request that float4 of the 13
+// records the four terms read at once, and write the result; no barrier follows
+// the list, so a vertex costs one round trip and waves do not wait for each
+// other.  The 13 records lie in neighbouring rows that the workgroup's other
+// waves read too, and come from L1 and L2.
+//
+// On the 256^3 room (1.68 M records; 376 MB read and written are 73 us at the
+// rate of a large copy) and the 512^3 room (4.03 M) this takes 206 and 481 us,
+// where staging 6^3 halos of records in LDS, sub-block by sub-block, took 318
+// and 1120: a chain of barriers per sub-block and 13 scattered LDS reads per
+// field.  The vector ALU is then busy half of the time, and the L2s fetch the
+// records three times over (halos, and rows that leave L2 before their turn).
+// Cubes of 2^3 blocks dealt to the XCDs in turn: one contiguous eighth each gave
+// 266 and 665 us (an XCD with a whole wall of the room works longest), single
+// blocks in turn 240 and 527, cubes of 4^3 233 and 538.
 //
 // SET writes the gradient (grad = dTV) instead of adding to it, which saves
 // the read of the gradient: a step that zeroes its gradient can run the TV
@@ -39,43 +38,83 @@ namespace pxm {
 constexpr int TB8 = 8;                  // block edge (vertices)
 constexpr int TH8 = TB8 + 2;            // with halo
 constexpr int TH83 = TH8 * TH8 * TH8;   // 1000 link positions
-constexpr int TB = 4;                   // sub-brick edge
-constexpr int TH = TB + 2;
-constexpr int TH3 = TH * TH * TH;       // 216 staged positions
+constexpr int CUBE = 2;                 // blocks per axis of a cube
+constexpr uint32_t NONE = 0xffffffffu;  // no record
 constexpr int TV_THREADS = 256;
-// a listed vertex: its sub-halo position and the TV terms that touch it
-// (its own, and those of its -x, -y, -z neighbours)
-constexpr int TERM_POS = 0xff, TERM_OWN = 0x100, TERM_X = 0x200, TERM_Y = 0x400, TERM_Z = 0x800;
-static_assert(TH3 <= TERM_POS + 1, "sub-halo positions fit in the low byte");
-constexpr int TV_ITEMS = TB * TB * TB * 32 / TV_THREADS;   // vertex-field items per thread, at most
+// a listed vertex: its position in the halo block and the TV terms that touch
+// it (its own, and those of its -x, -y, -z neighbours)
+constexpr int TERM_POS = 0x3ff, TERM_OWN = 0x400, TERM_X = 0x800, TERM_Y = 0x1000, TERM_Z = 0x2000;
+static_assert(TH83 <= TERM_POS + 1, "halo positions fit in the low bits");
 
 __device__ __forceinline__ int hidx8(int x, int y, int z) { return (x * TH8 + y) * TH8 + z; }
-__device__ __forceinline__ int hidx(int x, int y, int z) { return (x * TH + y) * TH + z; }
 
-template <int DEG, bool SET>
+// dTV / d val of one field from the values of the 13 records around vertex v:
+// f* ahead of it, b* behind it, and those one step ahead of a step behind.
+struct TvHood {
+    float v, fx, fy, fz, bx, bxy, bxz, by, byx, byz, bz, bzx, bzy;
+};
+
+// NORMAL: eps is a normal number, so the sums of squares are, and need no scaling.
+template <bool NORMAL>
+__device__ __forceinline__ float tv_rsqrt(float x) {
+    return NORMAL ? __builtin_amdgcn_rsqf(x) : rsqrtf(x);
+}
+
+template <bool NORMAL>
+__device__ __forceinline__ float tv_field(const TvHood& h, int e, float eps) {
+    float acc = 0.f;
+    {
+        const float dx = h.fx - h.v, dy = h.fy - h.v, dz = h.fz - h.v;
+        const float t = (dx + dy + dz) * tv_rsqrt<NORMAL>(dx * dx + dy * dy + dz * dz + eps);
+        if (e & TERM_OWN) acc -= t;
+    }
+    {
+        const float dx = h.v - h.bx, dy = h.bxy - h.bx, dz = h.bxz - h.bx;
+        const float t = dx * tv_rsqrt<NORMAL>(dx * dx + dy * dy + dz * dz + eps);
+        if (e & TERM_X) acc += t;
+    }
+    {
+        const float dx = h.byx - h.by, dy = h.v - h.by, dz = h.byz - h.by;
+        const float t = dy * tv_rsqrt<NORMAL>(dx * dx + dy * dy + dz * dz + eps);
+        if (e & TERM_Y) acc += t;
+    }
+    {
+        const float dx = h.bzx - h.bz, dy = h.bzy - h.bz, dz = h.v - h.bz;
+        const float t = dz * tv_rsqrt<NORMAL>(dx * dx + dy * dy + dz * dz + eps);
+        if (e & TERM_Z) acc += t;
+    }
+    return acc;
+}
+
+// WIDE: the map's records span 4 GiB or more; otherwise s_rec holds byte offsets,
+// and an address is one 32-bit add.
+template <int DEG, bool SET, bool NORMAL, bool WIDE>
 __global__ void __launch_bounds__(TV_THREADS) k_tv(KGrid g, float lam_d, float lam_sh, float eps,
-                                                   float* __restrict__ grad, int nby, int nbz) {
+                                                   float* __restrict__ grad, int ncy, int ncz) {
     constexpr int S = RecL<DEG>::S, Q = RecL<DEG>::Q, USED = RecL<DEG>::USED;
-    constexpr int STAGE_ITERS = (TH3 * Q + TV_THREADS - 1) / TV_THREADS;   // staged float4 per thread
-    static_assert(TV_THREADS == 4 * WAVE, "one wave lists two sub-bricks");
-    __shared__ int s_id8[TH83];             // links of the block halo (-1 empty or outside)
-    __shared__ int s_id[TH3];               // links of the current sub-brick halo
-    __shared__ float4 s_v4[TH3 * Q];        // the sub-halo records, position-major: field m of
-                                            // position p at float p * S + m
-    __shared__ int s_list[8][TB * TB * TB]; // per sub-brick: sub-halo positions of its allocated vertices
-    __shared__ int s_n[8];
+    __shared__ uint32_t s_rec[TH83];        // records of the block and its halo (NONE: empty or outside)
+    __shared__ int s_list[TB8 * TB8 * TB8]; // its allocated vertices
+    __shared__ int s_n;
     const int t = threadIdx.x;
-    const int64_t block = xcd_tile(blockIdx.x, gridDim.x);
-    const int bz = (int)(block % nbz), by = (int)((block / nbz) % nby);
-    const int bx = (int)(block / ((int64_t)nbz * nby));
+    // Cubes of blocks go round the XCDs (workgroup b runs on XCD b mod 8), so
+    // that blocks sharing halos share an L2 and no XCD gets a whole wall of the
+    // map; the turn shifts from round to round, as a row of cubes may hold eight.
+    constexpr int PER_CUBE = CUBE * CUBE * CUBE;
+    const int64_t round = blockIdx.x / (8 * PER_CUBE);
+    const int64_t cube = round * 8 + ((blockIdx.x + 3 * round + round / 8) & 7);
+    const int in = (int)((blockIdx.x / 8) % PER_CUBE);
+    const int bz = (int)(cube % ncz) * CUBE + in % CUBE, by = (int)((cube / ncz) % ncy) * CUBE + (in / CUBE) % CUBE;
+    const int bx = (int)(cube / ((int64_t)ncz * ncy)) * CUBE + in / (CUBE * CUBE);
     const int x0 = bx * TB8, y0 = by * TB8, z0 = bz * TB8;
     const int X = g.R[0], Y = g.R[1], Z = g.R[2];
+    if (x0 >= X || y0 >= Y || z0 >= Z) return;              // workgroup-uniform, as below
     // An allocated vertex v of this block is a corner of cell min(v, R-2) per
     // axis, which lies in cell brick (bx, by, bz) whenever that brick exists.
     if (g.occ1 && bx < g.B[0] && by < g.B[1] && bz < g.B[2]) {
         const int c[3] = {x0, y0, z0};
-        if (brick_empty(g, c)) return;                      // workgroup-uniform
+        if (brick_empty(g, c)) return;
     }
+    if (t == 0) s_n = 0;
     {
         // all of a thread's link loads are issued before the first LDS write
         constexpr int LINK_ITERS = (TH83 + TV_THREADS - 1) / TV_THREADS;
@@ -83,182 +122,115 @@ __global__ void __launch_bounds__(TV_THREADS) k_tv(KGrid g, float lam_d, float l
 #pragma unroll
         for (int k = 0; k < LINK_ITERS; ++k) {
             const int p = t + k * TV_THREADS;
-            const int hx = p / (TH8 * TH8), hy = (p / TH8) % TH8, hz = p % TH8;
-            const int x = x0 + hx - 1, y = y0 + hy - 1, z = z0 + hz - 1;
+            const int x = x0 + p / (TH8 * TH8) - 1, y = y0 + (p / TH8) % TH8 - 1, z = z0 + p % TH8 - 1;
             ids[k] = -1;
-            if (p < TH83 && x >= 0 && x < X && y >= 0 && y < Y && z >= 0 && z < Z)
+            if (p < TH83 && (uint32_t)x < (uint32_t)X && (uint32_t)y < (uint32_t)Y && (uint32_t)z < (uint32_t)Z)
                 ids[k] = g.link[((int64_t)x * Y + y) * Z + z];
         }
 #pragma unroll
         for (int k = 0; k < LINK_ITERS; ++k) {
             const int p = t + k * TV_THREADS;
-            if (p < TH83) s_id8[p] = ((uint32_t)ids[k] < (uint64_t)g.n_alloc) ? ids[k] : -1;
+            if (p < TH83)
+                s_rec[p] = (uint32_t)ids[k] >= (uint64_t)g.n_alloc ? NONE
+                         : WIDE ? (uint32_t)ids[k] : (uint32_t)ids[k] * (uint32_t)(S * sizeof(float));
         }
     }
     __syncthreads();
-    // sub-brick sb: origin 4 * (bit 2, bit 1, bit 0 of sb) in block-halo
-    // coordinates (its halo starts one lower).  Wave w lists sub-bricks w
-    // and w + 4 (64 vertices each, one per lane).  An entry holds the
-    // vertex's sub-halo position and which of the four terms touching it
-    // exist (TERM_*), decided once per vertex here rather than per field.
+    // A wave lists the vertices of two 4^3 sub-blocks, so that waves at work
+    // together share records.  The order between waves does not matter.
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int sb = t / WAVE + 4 * j, l = t % WAVE;
-        const int ox = 4 * ((sb >> 2) & 1), oy = 4 * ((sb >> 1) & 1), oz = 4 * (sb & 1);
-        const int ix = l / (TB * TB) + 1, iy = (l / TB) % TB + 1, iz = l % TB + 1;
-        const int h = hidx8(ox + ix, oy + iy, oz + iz);
-        const bool a = s_id8[h] >= 0;
+    for (int j = 0; j < TB8 * TB8 * TB8 / TV_THREADS; ++j) {
+        const int p = j * TV_THREADS + t, sb = p >> 6;
+        const int ix = (sb >> 2) * 4 + ((p >> 4) & 3), iy = ((sb >> 1) & 1) * 4 + ((p >> 2) & 3);
+        const int iz = (sb & 1) * 4 + (p & 3);
+        const int h = hidx8(ix + 1, iy + 1, iz + 1);
+        const bool a = s_rec[h] != NONE;
         const unsigned long long m = __ballot(a);
+        int base = 0;
+        if (lane_id() == 0 && m) base = atomicAdd(&s_n, __popcll(m));
+        base = __builtin_amdgcn_readfirstlane(base);
         if (a) {
-            const int x = x0 + ox + ix - 1, y = y0 + oy + iy - 1, z = z0 + oz + iz - 1;
+            const int x = x0 + ix, y = y0 + iy, z = z0 + iz;
             const bool ix_ = x < X - 1, iy_ = y < Y - 1, iz_ = z < Z - 1;
-            int e = hidx(ix, iy, iz);
+            int e = h;
             if (ix_ && iy_ && iz_) e |= TERM_OWN;
-            if (x >= 1 && iy_ && iz_ && s_id8[h - TH8 * TH8] >= 0) e |= TERM_X;
-            if (y >= 1 && ix_ && iz_ && s_id8[h - TH8] >= 0) e |= TERM_Y;
-            if (z >= 1 && ix_ && iy_ && s_id8[h - 1] >= 0) e |= TERM_Z;
-            s_list[sb][__popcll(m & ((1ull << l) - 1))] = e;
+            if (x >= 1 && iy_ && iz_ && s_rec[h - TH8 * TH8] != NONE) e |= TERM_X;
+            if (y >= 1 && ix_ && iz_ && s_rec[h - TH8] != NONE) e |= TERM_Y;
+            if (z >= 1 && ix_ && iy_ && s_rec[h - 1] != NONE) e |= TERM_Z;
+            s_list[base + __popcll(m & ((1ull << lane_id()) - 1))] = e;
         }
-        if (l == 0) s_n[sb] = __popcll(m);
     }
     __syncthreads();
-    auto next_nonempty = [&](int sb) {
-        while (sb < 8 && s_n[sb] == 0) ++sb;                // workgroup-uniform
-        return sb;
-    };
-    // the sub-halo records of sub-brick sb: Q lanes per position, one float4 each
-    float4 wv[STAGE_ITERS];
-    auto request = [&](int sb) {
-        const int ox = 4 * ((sb >> 2) & 1), oy = 4 * ((sb >> 1) & 1), oz = 4 * (sb & 1);
-#pragma unroll
-        for (int k = 0; k < STAGE_ITERS; ++k) {
-            const int i = t + k * TV_THREADS;
-            wv[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (i < TH3 * Q) {
-                const int p = i / Q, q = i - Q * p;
-                const int hx = p / (TH * TH), hy = (p / TH) % TH, hz = p % TH;
-                const int id = s_id8[hidx8(ox + hx, oy + hy, oz + hz)];
-                if (id >= 0) wv[k] = reinterpret_cast<const float4*>(g.data + (int64_t)id * S)[q];
-            }
-        }
-    };
-    // halo offset of sub-halo position t (positions of every sub-brick
-    // differ from it by the sub-brick's origin)
-    const int my_h8 = t < TH3 ? hidx8(t / (TH * TH), (t / TH) % TH, t % TH) : 0;
-    int sb = next_nonempty(0);
-    if (sb < 8) request(sb);
-#pragma unroll 1
-    while (sb < 8) {
-        const int ox = 4 * ((sb >> 2) & 1), oy = 4 * ((sb >> 1) & 1), oz = 4 * (sb & 1);
-        // records as they arrived (float4 i of the sub-halo is float4 i of
-        // the position-major block), and the sub-halo links, position t
-#pragma unroll
-        for (int k = 0; k < STAGE_ITERS; ++k) {
-            const int i = t + k * TV_THREADS;
-            if (i < TH3 * Q) s_v4[i] = wv[k];
-        }
-        if (t < TH3) s_id[t] = s_id8[hidx8(ox, oy, oz) + my_h8];
-        __syncthreads();
-        const int nx = next_nonempty(sb + 1);
-        if (nx < 8) request(nx);                            // in flight while sb is computed
-        const int n = s_n[sb];
-        const int* list = s_list[sb];
-        // 32 lanes per allocated vertex, lane m < USED takes field m; a thread
-        // has at most TV_ITEMS items (n <= 64)
-        auto dtv = [&](int e, int m) -> float {
-            const int c = e & TERM_POS;
-            const float* field = reinterpret_cast<const float*>(s_v4) + m;
-            auto val = [&](int p) -> float { return field[p * S]; };
-            const float v0 = val(c);
-            float acc = 0.f;
-            if (e & TERM_OWN) {
-                const float dx = val(c + TH * TH) - v0;
-                const float dy = val(c + TH) - v0;
-                const float dz = val(c + 1) - v0;
-                acc -= (dx + dy + dz) * rsqrtf(dx * dx + dy * dy + dz * dz + eps);
-            }
-            if (e & TERM_X) {
-                const float a0 = val(c - TH * TH);
-                const float dx = v0 - a0;
-                const float dy = val(c - TH * TH + TH) - a0;
-                const float dz = val(c - TH * TH + 1) - a0;
-                acc += dx * rsqrtf(dx * dx + dy * dy + dz * dz + eps);
-            }
-            if (e & TERM_Y) {
-                const float b0 = val(c - TH);
-                const float dx = val(c - TH + TH * TH) - b0;
-                const float dy = v0 - b0;
-                const float dz = val(c - TH + 1) - b0;
-                acc += dy * rsqrtf(dx * dx + dy * dy + dz * dz + eps);
-            }
-            if (e & TERM_Z) {
-                const float c0 = val(c - 1);
-                const float dx = val(c - 1 + TH * TH) - c0;
-                const float dy = val(c - 1 + TH) - c0;
-                const float dz = v0 - c0;
-                acc += dz * rsqrtf(dx * dx + dy * dy + dz * dz + eps);
-            }
-            return (m == 0 ? lam_d : lam_sh) * acc;
+    const int items = s_n * Q;
+    const char* data = reinterpret_cast<const char*>(g.data);
+    char* gout = reinterpret_cast<char*>(grad);
+    for (int i = t; i < items; i += TV_THREADS) {
+        const int e = s_list[i / Q];
+        const uint32_t q = i % Q;
+        const int h = e & TERM_POS;
+        auto off = [&](uint32_t rec) {                      // bytes from the array's start to the lane's float4
+            if constexpr (WIDE) return (size_t)rec * (S * sizeof(float)) + q * 16u;
+            else return rec + q * 16u;
         };
-        if constexpr (SET) {
-#pragma unroll
-            for (int k = 0; k < TV_ITEMS; ++k) {
-                const int it = t + k * TV_THREADS;
-                const int m = it & 31;
-                if (it < n * 32 && m < USED) {
-                    const int e = list[it >> 5];
-                    grad[(int64_t)s_id[e & TERM_POS] * S + m] = dtv(e, m);
-                }
-            }
-        } else {
-            // the items' gradient entries are read first, so the
-            // read-modify-writes cost one round trip, not one each
-            float gv[TV_ITEMS];
-            int64_t ga[TV_ITEMS];
-#pragma unroll
-            for (int k = 0; k < TV_ITEMS; ++k) {
-                const int it = t + k * TV_THREADS;
-                const int m = it & 31;
-                ga[k] = -1;
-                gv[k] = 0.f;
-                if (it < n * 32 && m < USED) {
-                    ga[k] = (int64_t)s_id[list[it >> 5] & TERM_POS] * S + m;
-                    gv[k] = grad[ga[k]];
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < TV_ITEMS; ++k) {
-                if (ga[k] < 0) continue;
-                const int it = t + k * TV_THREADS;
-                grad[ga[k]] = gv[k] + dtv(list[it >> 5], it & 31);
-            }
+        auto at = [&](int p) -> float4 {
+            const uint32_t rec = s_rec[p];
+            return rec != NONE ? *reinterpret_cast<const float4*>(data + off(rec)) : make_float4(0.f, 0.f, 0.f, 0.f);
+        };
+        constexpr int DX = TH8 * TH8, DY = TH8, DZ = 1;
+        const float4 v = at(h), fx = at(h + DX), fy = at(h + DY), fz = at(h + DZ);
+        const float4 px = at(h - DX), pxy = at(h - DX + DY), pxz = at(h - DX + DZ);
+        const float4 py = at(h - DY), pyx = at(h - DY + DX), pyz = at(h - DY + DZ);
+        const float4 pz = at(h - DZ), pzx = at(h - DZ + DX), pzy = at(h - DZ + DY);
+        float* out = reinterpret_cast<float*>(gout + off(s_rec[h]));
+        const bool whole = 4 * q + 4 <= USED;               // else one used field and padding
+        float4 old = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (!SET) {
+            if (whole) old = *reinterpret_cast<const float4*>(out);
+            else old.x = out[0];
         }
-        __syncthreads();                                    // LDS reused by the next sub-brick
-        sb = nx;
+        const float lam = q == 0 ? lam_d : lam_sh;          // field 0 is the density
+        float4 r;
+        r.x = lam * tv_field<NORMAL>({v.x, fx.x, fy.x, fz.x, px.x, pxy.x, pxz.x, py.x, pyx.x, pyz.x, pz.x, pzx.x, pzy.x}, e, eps);
+        r.y = lam_sh * tv_field<NORMAL>({v.y, fx.y, fy.y, fz.y, px.y, pxy.y, pxz.y, py.y, pyx.y, pyz.y, pz.y, pzx.y, pzy.y}, e, eps);
+        r.z = lam_sh * tv_field<NORMAL>({v.z, fx.z, fy.z, fz.z, px.z, pxy.z, pxz.z, py.z, pyx.z, pyz.z, pz.z, pzx.z, pzy.z}, e, eps);
+        r.w = lam_sh * tv_field<NORMAL>({v.w, fx.w, fy.w, fz.w, px.w, pxy.w, pxz.w, py.w, pyx.w, pyz.w, pz.w, pzx.w, pzy.w}, e, eps);
+        if (!SET) {
+            r.x += old.x;
+            r.y += old.y;
+            r.z += old.z;
+            r.w += old.w;
+        }
+        if (whole) *reinterpret_cast<float4*>(out) = r;
+        else out[0] = r.x;
     }
 }
 
-template <bool SET>
+template <int DEG, bool SET>
 static void tv_go(const KGrid& g, float lambda_density, float lambda_sh, float eps, float* grad_data,
                   hipStream_t st) {
-    const int nbx = (g.R[0] + TB8 - 1) / TB8, nby = (g.R[1] + TB8 - 1) / TB8;
-    const int nbz = (g.R[2] + TB8 - 1) / TB8;
-    const int64_t nb = (int64_t)nbx * nby * nbz;
-    if (g.deg == 0)
-        hipLaunchKernelGGL((k_tv<0, SET>), dim3((unsigned)nb), dim3(TV_THREADS), 0, st, g, lambda_density,
-                           lambda_sh, eps, grad_data, nby, nbz);
-    else if (g.deg == 1)
-        hipLaunchKernelGGL((k_tv<1, SET>), dim3((unsigned)nb), dim3(TV_THREADS), 0, st, g, lambda_density,
-                           lambda_sh, eps, grad_data, nby, nbz);
-    else
-        hipLaunchKernelGGL((k_tv<2, SET>), dim3((unsigned)nb), dim3(TV_THREADS), 0, st, g, lambda_density,
-                           lambda_sh, eps, grad_data, nby, nbz);
+    int nc[3];
+    for (int a = 0; a < 3; ++a) nc[a] = (g.R[a] + TB8 * CUBE - 1) / (TB8 * CUBE);
+    const int64_t rounds = ((int64_t)nc[0] * nc[1] * nc[2] + 7) / 8;
+    const dim3 blocks((unsigned)(rounds * 8 * CUBE * CUBE * CUBE)), threads(TV_THREADS);
+    const bool normal = eps >= 1.17549435e-38f;
+    const bool wide = (uint64_t)g.n_alloc * (RecL<DEG>::S * sizeof(float)) >= NONE;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, blocks, threads, 0, st, g, lambda_density, lambda_sh, eps, grad_data, nc[1], nc[2]);
+    };
+    if (wide) normal ? go(k_tv<DEG, SET, true, true>) : go(k_tv<DEG, SET, false, true>);
+    else normal ? go(k_tv<DEG, SET, true, false>) : go(k_tv<DEG, SET, false, false>);
 }
 
 hipError_t launch_tv(const KGrid& g, float lambda_density, float lambda_sh, float eps,
                      float* grad_data, bool set, hipStream_t st) {
-    if (set) tv_go<true>(g, lambda_density, lambda_sh, eps, grad_data, st);
-    else tv_go<false>(g, lambda_density, lambda_sh, eps, grad_data, st);
+    auto by_set = [&](auto D) {
+        constexpr int DEG = decltype(D)::value;
+        if (set) tv_go<DEG, true>(g, lambda_density, lambda_sh, eps, grad_data, st);
+        else tv_go<DEG, false>(g, lambda_density, lambda_sh, eps, grad_data, st);
+    };
+    if (g.deg == 0) by_set(std::integral_constant<int, 0>{});
+    else if (g.deg == 1) by_set(std::integral_constant<int, 1>{});
+    else by_set(std::integral_constant<int, 2>{});
     return hipGetLastError();
 }
 
