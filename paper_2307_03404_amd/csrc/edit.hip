@@ -40,7 +40,6 @@ constexpr int KEEP_ITERS = EDIT_CHUNK / EDIT_THREADS;   // records per thread in
 constexpr int SCAN_THREADS = 1024;
 constexpr int LINK_PER_THREAD = 8;
 constexpr int LINK_ITEMS = LINK_PER_THREAD * EDIT_THREADS;   // link-table items per workgroup pass
-constexpr int UNIT_BATCHES = 4;                         // 8-vertex batches a wave requests at once
 static_assert(EDIT_WORDS == EDIT_THREADS, "one thread per flag word of a chunk");
 
 __device__ __forceinline__ bool link_ok(int32_t l, int64_t n) { return (uint32_t)l < (uint64_t)n; }
@@ -225,6 +224,15 @@ __device__ __forceinline__ uint64_t coarse_window(const uint32_t* vbits, int64_t
     return (lo | (hi << 32)) >> sh;
 }
 
+// Bits 0 .. 15 of x at the even positions 0 .. 30.
+__device__ __forceinline__ uint32_t spread16(uint32_t x) {
+    x &= 0xffffu;
+    x = (x | (x << 8)) & 0x00ff00ffu;
+    x = (x | (x << 4)) & 0x0f0f0f0fu;
+    x = (x | (x << 2)) & 0x33333333u;
+    return (x | (x << 1)) & 0x55555555u;
+}
+
 // One thread per fine flag word: fine row (fx, fy), fine z in [32 l, 32 l + 32).
 // Window bit k is coarse z = 16 l - 1 + k; fine z = 32 l + j sits on or after
 // coarse vertex 16 l + (j >> 1), window bit (j >> 1) + 1.
@@ -245,119 +253,224 @@ __global__ __launch_bounds__(EDIT_THREADS) void k_grow_flags(const uint32_t* __r
             for (int y = y0; y <= y1; ++y) W |= coarse_window(vbits, (int64_t)x * L.R[1] + y, L.WC, 16 * l - 1);
         const uint64_t D2 = W | (W >> 1);     // bit k: coarse k or k+1   (odd fine z)
         const uint64_t D3 = D2 | (W << 1);    // bit k: coarse k-1 .. k+1 (even fine z)
-        const int jend = min(32, L.Rf[2] - 32 * l);
-        for (int j = 0; j < jend; ++j) {
-            const int k = (j >> 1) + 1;
-            bits |= (uint32_t)((((j & 1) ? D2 : D3) >> k) & 1ull) << j;
-        }
+        // fine z = 32 l + 2 i takes bit i + 1 of D3, 32 l + 2 i + 1 that of D2
+        bits = spread16((uint32_t)(D3 >> 1)) | (spread16((uint32_t)(D2 >> 1)) << 1);
+        const int in_row = L.Rf[2] - 32 * l;
+        if (in_row < 32) bits &= (1u << in_row) - 1u;
     }
     finish_chunk(bits, gw, nw, words, wpre, chunk_total);
 }
 
-// One lane per padded fine item; items past the row's end are padding.  A
-// thread takes LINK_PER_THREAD items and issues all their loads first.
-__global__ __launch_bounds__(EDIT_THREADS) void k_fine_link(Lattice L, int64_t n_items,
-                                                            const uint32_t* __restrict__ words,
+// One wave per fine row, 4 links per lane and ROW_STEPS steps of 256 requested
+// together: the row is the same on the whole wave, so a link costs a shift, a
+// popcount and a quarter of a store.  Bound by the writes: 511^3 links 115 us (537 MB
+// written), 220 where each lane found the row of its link by division.
+constexpr int ROW_STEPS = 2;
+
+__global__ __launch_bounds__(EDIT_THREADS) void k_fine_link(Lattice L, const uint32_t* __restrict__ words,
                                                             const int32_t* __restrict__ wpre,
                                                             const int32_t* __restrict__ chunk_off,
                                                             int32_t* __restrict__ link_fine) {
-    // neighbouring passes share cache lines of link_fine: keep them on one XCD
-    const int64_t stride = (int64_t)gridDim.x * LINK_ITEMS;
-    for (int64_t i0 = xcd_tile(blockIdx.x, gridDim.x) * LINK_ITEMS; i0 < n_items; i0 += stride) {
-        uint32_t bits[LINK_PER_THREAD];
-        int32_t base[LINK_PER_THREAD];
+    const int lane = lane_id();
+    const int64_t rows = (int64_t)L.Rf[0] * L.Rf[1];
+    const int64_t waves = (int64_t)gridDim.x * (EDIT_THREADS / WAVE);
+    for (int64_t row = (int64_t)blockIdx.x * (EDIT_THREADS / WAVE) + threadIdx.x / WAVE; row < rows; row += waves) {
+        const int64_t w0 = row * L.WF;
+        int32_t* out = link_fine + row * L.Rf[2];
+        for (int z0 = 0; z0 < L.Rf[2]; z0 += ROW_STEPS * WAVE * 4) {
+            uint32_t bits[ROW_STEPS];
+            int32_t base[ROW_STEPS];
 #pragma unroll
-        for (int k = 0; k < LINK_PER_THREAD; ++k) {
-            const int64_t i = i0 + k * EDIT_THREADS + threadIdx.x;
-            bits[k] = 0u;
-            base[k] = 0;
-            if (i < n_items) {
-                const int64_t w = i >> 5;
-                bits[k] = words[w];
-                base[k] = chunk_off[w / EDIT_WORDS] + wpre[w];
+            for (int k = 0; k < ROW_STEPS; ++k) {
+                const int z = z0 + (k * WAVE + lane) * 4;
+                bits[k] = 0u;
+                base[k] = 0;
+                if (z < L.Rf[2]) {
+                    const int64_t w = w0 + (z >> 5);
+                    bits[k] = words[w];
+                    base[k] = chunk_off[w / EDIT_WORDS] + wpre[w];
+                }
             }
-        }
 #pragma unroll
-        for (int k = 0; k < LINK_PER_THREAD; ++k) {
-            const int64_t i = i0 + k * EDIT_THREADS + threadIdx.x;
-            const uint32_t w = (uint32_t)(i >> 5);
-            const uint32_t row = w / (uint32_t)L.WF;
-            const int fz = (int)(w - row * (uint32_t)L.WF) * 32 + (int)(i & 31);
-            const int b = (int)(i & 31);
-            if (i < n_items && fz < L.Rf[2])
-                link_fine[(int64_t)row * L.Rf[2] + fz] =
-                    ((bits[k] >> b) & 1u) ? base[k] + __popc(bits[k] & ((1u << b) - 1u)) : -1;
+            for (int k = 0; k < ROW_STEPS; ++k) {
+                const int z = z0 + (k * WAVE + lane) * 4, b = z & 31;
+                int32_t id = base[k] + __popc(bits[k] & ((1u << b) - 1u));
+                int32_t l[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const bool on = (bits[k] >> (b + j)) & 1u;
+                    l[j] = on ? id : -1;
+                    id += on;
+                }
+                if (z + 4 <= L.Rf[2]) {
+                    __builtin_memcpy(out + z, l, 16);        // 16 bytes at any multiple of 4
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (z + j < L.Rf[2]) out[z + j] = l[j];
+                }
+            }
         }
     }
 }
 
+// Component c of the eight fine records: sums over corners in (x, y, z) bit order,
+// an empty corner 0, in FP64, scaled by their power of two at the end (which
+// rounds as scaling each term would) and rounded once to FP32.  A sum of two
+// is the FP32 sum: rounding it to 53 bits first changes nothing.  Sums share
+// their common beginnings.
+__device__ __forceinline__ void fine_values(const float v[8][4], int c, float scale, float r[8][4]) {
+    const float z = 0.f + v[0][c];                          // a sum starts at +0
+    const float h = 0.5f * scale;
+    const double q = 0.25 * (double)scale, e = 0.125 * (double)scale;
+    double d[8];
+#pragma unroll
+    for (int b = 0; b < 8; ++b) d[b] = (double)v[b][c];
+    const double s0 = (double)z, s01 = s0 + d[1], s3 = s01 + d[2] + d[3];
+    r[0][c] = z * scale;
+    r[1][c] = (z + v[1][c]) * h;
+    r[2][c] = (z + v[2][c]) * h;
+    r[3][c] = (float)(s3 * q);
+    r[4][c] = (z + v[4][c]) * h;
+    r[5][c] = (float)((s01 + d[4] + d[5]) * q);
+    r[6][c] = (float)((s0 + d[2] + d[4] + d[6]) * q);
+    r[7][c] = (float)((s3 + d[4] + d[5] + d[6] + d[7]) * e);
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+constexpr uint32_t NOWHERE = 0xffffffffu;   // no record: beyond every buffer
+
+// Float4s of an array of records, by byte offset.  Not WIDE: a buffer resource of
+// the array's size (under 4 GiB), past whose end a load gives 0 and a store does
+// nothing, so neither needs a branch.  WIDE: record ids and pointers.
+template <bool WIDE>
+struct Records {
+    float4* base;
+    int Q;
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ Records(void* p, int64_t n, int S) : base(static_cast<float4*>(p)), Q(S / 4) {
+        rsrc = __builtin_amdgcn_make_buffer_rsrc(p, 0, WIDE ? 0 : (int)(uint32_t)(n * S * 4), 0x00020000);
+    }
+    // what the list holds for a record id
+    __device__ static uint32_t key(int32_t id, int S) {
+        return id < 0 ? NOWHERE : WIDE ? (uint32_t)id : (uint32_t)id * (uint32_t)(4 * S);
+    }
+    __device__ f32x4 load(uint32_t key, uint32_t part) const {
+        if constexpr (WIDE) {
+            if (key == NOWHERE) return f32x4{0.f, 0.f, 0.f, 0.f};
+            return *reinterpret_cast<const f32x4*>(base + (int64_t)key * Q + part);
+        } else {
+            return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, key == NOWHERE ? key : key + 16 * part, 0, 0));
+        }
+    }
+    __device__ void store(uint32_t key, uint32_t part, f32x4 v) const {
+        if constexpr (WIDE) {
+            if (key != NOWHERE) *reinterpret_cast<f32x4*>(base + (int64_t)key * Q + part) = v;
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rsrc, key == NOWHERE ? key : key + 16 * part, 0, 0);
+        }
+    }
+};
+
 // Records by coarse vertex: coarse vertex v owns the fine vertices
 // 2v + o, o in {0,1}^3, and all eight interpolate from the corners v + o' of
-// coarse cell v (o' a subset of o's bits; weight 1/2 per odd axis).  A group
-// of 8 lanes takes one v: lane k first fetches corner link v + o_k and the id
-// of fine vertex 2v + o_k, for UNIT_BATCHES batches of 8 vertices at once;
-// then, per batch with an allocated fine vertex, lane p < S/4 (7 at SH degree
-// 2) fetches float4 p of the 8 corner records and writes float4 p of each
-// allocated fine record.
-// Sums run over corners in (x, y, z) bit order in FP64.
+// coarse cell v (o' a subset of o's bits; weight 1/2 per odd axis).  A wave
+// takes 64 coarse vertices of one row, a lane each: it reads their fine links
+// and lists, in LDS, the records around those with an allocated fine vertex (a
+// tenth of a sparse map's).  Then a group of 8 lanes takes a listed vertex: lane
+// p < S/4 (7 at SH degree 2) fetches float4 p of the 8 corner records and writes
+// float4 p of each allocated fine record.
+// 256^3 room to 511^3, 19.9 M records of 112 bytes: 1015 us (listing 200), of
+// which the writes alone, filled in order, would take 408; 8 lanes for every
+// coarse vertex, with branches around each corner and record, took 1446.
+// Requesting the next vertex's records early, two z-neighbours' records in one
+// store and other orders over the XCDs were no faster.
+template <bool WIDE>
 __global__ __launch_bounds__(EDIT_THREADS) void k_fine_data(KGrid g, Lattice L, const int32_t* __restrict__ link_fine,
                                                             int64_t n_fine, float* __restrict__ out) {
-    const int lane = lane_id(), k = lane & 7, gbase = lane & ~7;
-    const int64_t nc = (int64_t)L.R[0] * L.R[1] * L.R[2];
+    __shared__ u32x4 s_keys[EDIT_THREADS / WAVE][WAVE][4];   // per listed vertex: 8 corner records, 8 fine records
+    const int lane = lane_id(), wave = threadIdx.x / WAVE;
+    const int segs = (L.R[2] + WAVE - 1) / WAVE;             // 64-vertex segments per row
+    const int64_t items = (int64_t)L.R[0] * L.R[1] * segs;
     const int64_t waves = (int64_t)gridDim.x * (EDIT_THREADS / WAVE);
-    const float4* data4 = reinterpret_cast<const float4*>(g.data);
-    const int S = record_floats(g.deg), Q = S / 4;   // float4 parts per record (at most 7)
-    // neighbouring units write records that share cache lines: keep them on one XCD
-    const int64_t first = xcd_tile(blockIdx.x, gridDim.x) * (EDIT_THREADS / WAVE) + threadIdx.x / WAVE;
-    for (int64_t s = first; s * 8 * UNIT_BATCHES < nc; s += waves) {
-        int32_t lids[UNIT_BATCHES], fids[UNIT_BATCHES];
+    const int S = record_floats(g.deg), Q = S / 4;           // float4 parts per record (at most 7)
+    const Records<WIDE> src(const_cast<float*>(g.data), g.n_alloc, S), dst(out, n_fine, S);
+    for (int64_t it = ray_tile(blockIdx.x, gridDim.x) * (EDIT_THREADS / WAVE) + wave; it < items; it += waves) {
+        const int64_t row = it / segs;
+        const int vx = (int)(row / L.R[1]), vy = (int)(row - (int64_t)vx * L.R[1]);
+        const int vz = (int)(it - row * segs) * WAVE + lane;
+        int32_t l[8], f[8];
+        bool any = false;
 #pragma unroll
-        for (int j = 0; j < UNIT_BATCHES; ++j) {
-            const int64_t u = (s * UNIT_BATCHES + j) * 8 + (lane >> 3);
-            lids[j] = fids[j] = -1;
-            if (u < nc) {
-                const uint32_t r = (uint32_t)u / (uint32_t)L.R[2];   // u < R^3 < 2^31 / 8
-                const int vz = (int)((uint32_t)u - r * (uint32_t)L.R[2]);
-                const int vx = (int)(r / (uint32_t)L.R[1]), vy = (int)(r - (uint32_t)vx * L.R[1]);
-                const int ox = (k >> 2) & 1, oy = (k >> 1) & 1, oz = k & 1;
-                if (vx + ox < L.R[0] && vy + oy < L.R[1] && vz + oz < L.R[2]) {
-                    lids[j] = g.link[(int64_t)(vx + ox) * g.sx + (int64_t)(vy + oy) * g.sy + (vz + oz)];
-                    fids[j] = link_fine[((int64_t)(2 * vx + ox) * L.Rf[1] + (2 * vy + oy)) * L.Rf[2] + (2 * vz + oz)];
-                }
+        for (int o = 0; o < 8; o += 2) {                     // z pairs, 8 bytes at any multiple of 4
+            const int ox = o >> 2, oy = (o >> 1) & 1;
+            const int32_t* pair = link_fine + ((int64_t)(2 * vx + ox) * L.Rf[1] + (2 * vy + oy)) * L.Rf[2] + 2 * vz;
+            f[o] = f[o + 1] = -1;
+            if (vx + ox < L.R[0] && vy + oy < L.R[1]) {
+                if (vz + 1 < L.R[2]) __builtin_memcpy(f + o, pair, 8);
+                else if (vz < L.R[2]) f[o] = pair[0];
             }
         }
 #pragma unroll
-        for (int j = 0; j < UNIT_BATCHES; ++j) {
-            const int32_t lid = lids[j], fid = fids[j];
-            if (__ballot(link_ok(fid, n_fine)) == 0ull) continue;
-            const int p = k;   // float4 part handled by this lane (none when p >= Q)
-            float4 v[8];
-            bool ok[8];
+        for (int o = 0; o < 8; ++o) {
+            if (!link_ok(f[o], n_fine)) f[o] = -1;
+            any |= f[o] >= 0;
+        }
+        const unsigned long long m = __ballot(any);
+        if (m == 0ull) continue;
+        if (any) {
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
-                const int32_t lb = __shfl(lid, gbase + b, WAVE);
-                ok[b] = link_ok(lb, g.n_alloc);
-                v[b] = (ok[b] && p < Q) ? data4[(int64_t)lb * Q + p] : make_float4(0.f, 0.f, 0.f, 0.f);
+                const int ox = b >> 2, oy = (b >> 1) & 1, oz = b & 1;
+                l[b] = -1;
+                if (vx + ox < L.R[0] && vy + oy < L.R[1] && vz + oz < L.R[2])
+                    l[b] = g.link[(int64_t)(vx + ox) * g.sx + (int64_t)(vy + oy) * g.sy + (vz + oz)];
             }
 #pragma unroll
-            for (int o = 0; o < 8; ++o) {
-                const int32_t fo = __shfl(fid, gbase + o, WAVE);
-                if (!link_ok(fo, n_fine) || p >= Q) continue;
-                const double wt = 1.0 / (double)(1 << __popc(o));
-                double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-#pragma unroll
-                for (int b = 0; b < 8; ++b) {
-                    if ((b & ~o) || !ok[b]) continue;
-                    a0 += wt * (double)v[b].x;
-                    a1 += wt * (double)v[b].y;
-                    a2 += wt * (double)v[b].z;
-                    a3 += wt * (double)v[b].w;
-                }
-                if (p == 0) a0 *= 0.5;
-                reinterpret_cast<float4*>(out + (int64_t)fo * S)[p] =
-                    make_float4((float)a0, (float)a1, (float)a2, (float)a3);
-            }
+            for (int b = 0; b < 8; ++b) l[b] = link_ok(l[b], g.n_alloc) ? l[b] : -1;
+            u32x4* e = s_keys[wave][__popcll(m & ((1ull << lane) - 1))];
+            auto key4 = [&](const int32_t* id) {
+                return u32x4{src.key(id[0], S), src.key(id[1], S), src.key(id[2], S), src.key(id[3], S)};
+            };
+            e[0] = key4(l);
+            e[1] = key4(l + 4);
+            e[2] = key4(f);
+            e[3] = key4(f + 4);
         }
+        // the list is this wave's own: order its LDS writes before the reads
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int n = __popcll(m), p = lane & 7;
+        for (int base = 0; base < n; base += WAVE / 8) {
+            const int i = base + (lane >> 3);
+            u32x4 l0 = u32x4(NOWHERE), l1 = u32x4(NOWHERE);
+            if (i < n && p < Q) {
+                l0 = s_keys[wave][i][0];
+                l1 = s_keys[wave][i][1];
+            }
+            f32x4 cur[8];
+#pragma unroll
+            for (int b = 0; b < 8; ++b) cur[b] = src.load(b < 4 ? l0[b & 3] : l1[b & 3], p);
+            u32x4 f0 = u32x4(NOWHERE), f1 = u32x4(NOWHERE);
+            if (i < n && p < Q) {
+                f0 = s_keys[wave][i][2];
+                f1 = s_keys[wave][i][3];
+            }
+            float v[8][4], r[8][4];
+#pragma unroll
+            for (int b = 0; b < 8; ++b)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[b][c] = cur[b][c];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) fine_values(v, c, c == 0 && p == 0 ? 0.5f : 1.f, r);   // the density is halved
+#pragma unroll
+            for (int o = 0; o < 8; ++o)
+                dst.store(o < 4 ? f0[o & 3] : f1[o & 3], p, f32x4{r[o][0], r[o][1], r[o][2], r[o][3]});
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the next list overwrites this one
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -431,7 +544,7 @@ hipError_t launch_upsample_link(const KGrid& g, int32_t* link_fine, int64_t* n_f
                        c.wpre, c.chunk);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = scan(c, n_fine, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_fine_link, dim3(stride_blocks(nw * 32, LINK_ITEMS)), dim3(EDIT_THREADS), 0, st, L, nw * 32, c.words,
+    hipLaunchKernelGGL(k_fine_link, dim3(stride_blocks(rows_f, EDIT_THREADS / WAVE)), dim3(EDIT_THREADS), 0, st, L, c.words,
                        c.wpre, c.chunk, link_fine);
     return hipGetLastError();
 }
@@ -439,9 +552,10 @@ hipError_t launch_upsample_link(const KGrid& g, int32_t* link_fine, int64_t* n_f
 hipError_t launch_upsample_data(const KGrid& g, const int32_t* link_fine, int64_t n_fine, float* data_fine,
                                 hipStream_t st) {
     const Lattice L = lattice(g);
-    const int64_t units = (int64_t)L.R[0] * L.R[1] * L.R[2];   // coarse vertices, 8 lanes each
-    hipLaunchKernelGGL(k_fine_data, dim3(stride_blocks(units * 8, EDIT_THREADS * UNIT_BATCHES)), dim3(EDIT_THREADS), 0, st, g, L, link_fine, n_fine,
-                       data_fine);
+    const int64_t items = (int64_t)L.R[0] * L.R[1] * ((L.R[2] + WAVE - 1) / WAVE);   // a wave each
+    const uint64_t bytes = (uint64_t)(g.n_alloc > n_fine ? g.n_alloc : n_fine) * (4 * record_floats(g.deg));
+    hipLaunchKernelGGL(bytes < NOWHERE ? k_fine_data<false> : k_fine_data<true>, dim3(stride_blocks(items, EDIT_THREADS / WAVE)), dim3(EDIT_THREADS), 0, st, g, L, link_fine,
+                       n_fine, data_fine);
     return hipGetLastError();
 }
 

@@ -24,30 +24,44 @@ void occ_layout(const int R[3], int64_t& w0_words, int Q[3], int B[3], int64_t& 
     w1_words = ((int64_t)B[0] * B[1] * B[2] + 31) / 32;
 }
 
-// One wave per 4^3 block, one lane per cell (lane = bit); each lane requests
-// its 8 corner links at once, and the wave's ballot is the block's word.
-__global__ void k_occ0(KGrid g, uint64_t* __restrict__ occ0, int64_t n_blocks) {
+// A wave per 4 x 4 cells of (x, y) and OCC_RUN blocks along z: the 5 x 5 rows of 64
+// links it needs are requested at once, each row's ballot is its allocation bits,
+// a cell's bit along z is its own or the next, rows of cells are ORs of four
+// rows of vertices, and lane l assembles the word of block l.  Bound by the
+// link reads (511^3: 152 us; a lane per cell that read its own 8 corners took 506,
+// reading the table once takes 105).
+constexpr int OCC_RUN = 15;                                 // 60 cells, 61 of the 64 vertices
+
+__global__ void __launch_bounds__(256) k_occ0(KGrid g, uint64_t* __restrict__ occ0, int64_t n_items, int runs) {
     const int lane = lane_id();
     const int64_t waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
-    const int cx0 = lane >> 4, cy0 = (lane >> 2) & 3, cz0 = lane & 3;
-    for (int64_t q = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE; q < n_blocks;
-         q += waves) {
-        const int qz = (int)(q % g.Q[2]);
-        const int qy = (int)((q / g.Q[2]) % g.Q[1]);
-        const int qx = (int)(q / ((int64_t)g.Q[2] * g.Q[1]));
-        const int cx = 4 * qx + cx0, cy = 4 * qy + cy0, cz = 4 * qz + cz0;
-        bool occ = false;
-        if (cx < g.R[0] - 1 && cy < g.R[1] - 1 && cz < g.R[2] - 1) {
-            const int64_t c = (int64_t)cx * g.sx + (int64_t)cy * g.sy + cz;
-            int32_t l[8];
+    for (int64_t it = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE; it < n_items; it += waves) {
+        const int64_t q2 = it / runs;
+        const int qz = (int)(it - q2 * runs) * OCC_RUN;
+        const int qx = (int)(q2 / g.Q[1]), qy = (int)(q2 - (int64_t)qx * g.Q[1]);
+        const int x0 = 4 * qx, y0 = 4 * qy, z = 4 * qz + lane;
+        int32_t l[25];
 #pragma unroll
-            for (int b = 0; b < 8; ++b)
-                l[b] = g.link[c + ((b >> 2) & 1) * g.sx + ((b >> 1) & 1) * g.sy + (b & 1)];
-#pragma unroll
-            for (int b = 0; b < 8; ++b) occ |= (uint32_t)l[b] < (uint64_t)g.n_alloc;
+        for (int k = 0; k < 25; ++k) {
+            const int x = x0 + k / 5, y = y0 + k % 5;
+            l[k] = -1;
+            if (x < g.R[0] && y < g.R[1] && z < g.R[2]) l[k] = g.link[(int64_t)x * g.sx + (int64_t)y * g.sy + z];
         }
-        const unsigned long long m = __ballot(occ);
-        if (lane == 0) occ0[q] = (uint64_t)m;
+        unsigned long long row[25];
+#pragma unroll
+        for (int k = 0; k < 25; ++k) row[k] = __ballot((uint32_t)l[k] < (uint64_t)g.n_alloc);
+        // cells beyond R - 2 on an axis are empty
+        const int cells = g.R[2] - 1 - 4 * qz;
+        const unsigned long long in_z = cells >= 64 ? ~0ull : (1ull << cells) - 1ull;
+        uint64_t word = 0ull;
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+            const int cx = c >> 2, cy = c & 3, k = 5 * cx + cy;
+            unsigned long long m = row[k] | row[k + 1] | row[k + 5] | row[k + 6];
+            m = x0 + cx < g.R[0] - 1 && y0 + cy < g.R[1] - 1 ? (m | (m >> 1)) & in_z : 0ull;
+            word |= ((m >> (4 * (lane & 15))) & 0xfull) << (4 * c);
+        }
+        if (lane < OCC_RUN && qz + lane < g.Q[2]) occ0[q2 * g.Q[2] + qz + lane] = word;
     }
 }
 
@@ -83,10 +97,11 @@ hipError_t launch_occupancy(const KGrid& g, uint32_t* occ, hipStream_t st) {
         k.Q[a] = Q[a];
         k.B[a] = B[a];
     }
-    const int64_t n_blocks = w0 / 2;
-    const int64_t wgs = (n_blocks + 3) / 4;               // four waves per workgroup
+    const int runs = (Q[2] + OCC_RUN - 1) / OCC_RUN;
+    const int64_t n_items = (int64_t)Q[0] * Q[1] * runs;
+    const int64_t wgs = (n_items + 3) / 4;                // four waves per workgroup
     hipLaunchKernelGGL(k_occ0, dim3((unsigned)(wgs < (1 << 20) ? wgs : (1 << 20))), dim3(256), 0, st, k,
-                       reinterpret_cast<uint64_t*>(occ), n_blocks);
+                       reinterpret_cast<uint64_t*>(occ), n_items, runs);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t nb = (int64_t)B[0] * B[1] * B[2];
