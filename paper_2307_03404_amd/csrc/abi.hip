@@ -91,6 +91,7 @@ pxm::KGrid kgrid(const pxm_grid* g) {
     k.vs = g->voxel_size;
     k.inv_vs = 1.0 / (double)g->voxel_size;
     k.n_alloc = g->n_alloc;
+    k.probe = 2.0L * g->n_alloc > (long double)g->reso[0] * g->reso[1] * g->reso[2];
     k.link = g->link;
     k.data = g->data;
     int64_t w0, w1;

@@ -38,8 +38,8 @@ struct FwdResult {
 // count as kept positions.
 //
 // With a non-null `marks` the march also records, for the backward of the
-// same kernel, which of its positions passed the occupancy tests (the only
-// ones the backward has work at): bit o of the lane's mask is set for
+// same kernel, which of its positions carry light (the only ones the backward
+// has work at): bit o of the lane's mask is set for
 // position k_first + o, in words marks[w * WAVE] (w < MARK_WORDS) written
 // in order from a register; out.mark_last is the last word written and
 // out.mark_overflow is set if a marked position lay beyond the mask.
@@ -84,8 +84,21 @@ __device__ __forceinline__ void ray_forward(const KGrid& g, const KOpts& op, con
                     continue;
                 }
             }
+            ++n;
+            ++k;
+            int idx[8];
+            const int na = load_links(g, s.base, idx);
+            if (na == 0) continue;
+            ++occ;
+            occc += na;
+            if (g.probe && !(gather_density<DEG>(g, idx, s.f) > 0.f)) continue;
+            Interp v;
+            gather_interp<false, false, DEG>(g, idx, Y, nullptr, s.f, v);
+            const float sr = v.sig, s0 = v.s[0], s1 = v.s[1], s2 = v.s[2];
+            if (!(sr > 0.f)) continue;
+            gradc += na;
             if (marks) {
-                const int64_t o = k - ray.k_first;
+                const int64_t o = k - 1 - ray.k_first;
                 if (o >= (int64_t)MARK_WORDS * 32) {
                     movf = true;
                 } else {
@@ -98,18 +111,6 @@ __device__ __forceinline__ void ray_forward(const KGrid& g, const KOpts& op, con
                     mbits |= 1u << (int)(o & 31);
                 }
             }
-            ++n;
-            ++k;
-            int idx[8];
-            const int na = load_links(g, s.base, idx);
-            if (na == 0) continue;
-            Interp v;
-            gather_interp<false, false, DEG>(g, idx, Y, nullptr, s.f, v);
-            const float sr = v.sig, s0 = v.s[0], s1 = v.s[1], s2 = v.s[2];
-            ++occ;
-            occc += na;
-            if (!(sr > 0.f)) continue;
-            gradc += na;
             const float x = sr * delta;
             const float wt = T * (-expm1f(-x));
             C0 = fma((double)wt, (double)act_fwd(op.act, s0), C0);
@@ -144,8 +145,9 @@ struct BwdState {
 
 // Backward work of one occupied sample (Eq. 6-14): updates the running state
 // and the pose accumulators; returns true with the sample's grid-gradient
-// factors (gsig = dL/d sigma_raw, gs = dL/ds_c) when it carries light.
-template <bool POSE, bool VIEW, int DEG>
+// factors (gsig = dL/d sigma_raw, gs = dL/ds_c) when it carries light.  PROBE:
+// the position is not known to carry light.
+template <bool POSE, bool VIEW, int DEG, bool PROBE>
 __device__ __forceinline__ bool backward_sample(const KGrid& g, const KOpts& op, const Ray& ray,
                                                 const float Y[9], const float GY[9][3],
                                                 const Sample& s, const double Chat[3], double Dhat,
@@ -153,6 +155,7 @@ __device__ __forceinline__ bool backward_sample(const KGrid& g, const KOpts& op,
                                                 PoseAcc& pa, int idx[8], float w[8], float& gsig,
                                                 float gs[3]) {
     if (load_links(g, s.base, idx) == 0) return false;
+    if (PROBE && g.probe && !(gather_density<DEG>(g, idx, s.f) > 0.f)) return false;
     Interp v;
     gather_interp<POSE, POSE && VIEW, DEG>(g, idx, Y, GY, s.f, v);
     trilinear_weights(s.f, w);
@@ -269,7 +272,7 @@ __device__ __forceinline__ void ray_backward(const KGrid& g, const KOpts& op, co
             float gsig = 0.f, gs[3] = {0.f, 0.f, 0.f};
             Sample s;
             if (work && sample_at(g, ray, k, s))
-                have = backward_sample<POSE, VIEW, DEG>(g, op, ray, Y, GY, s, Chat, Dhat, gC, gDr, st,
+                have = backward_sample<POSE, VIEW, DEG, false>(g, op, ray, Y, GY, s, Chat, Dhat, gC, gDr, st,
                                                    pa, idx, w, gsig, gs);
             scatter_merged<DEG, FIX>(have, s.base, idx, w, gsig, gs, Y, wc, grad);
             if (work) off = next_mark(marks, mark_last, off + 1);
@@ -309,7 +312,7 @@ __device__ __forceinline__ void ray_backward(const KGrid& g, const KOpts& op, co
             float w[8];
             float gsig = 0.f, gs[3] = {0.f, 0.f, 0.f};
             if (work)
-                have = backward_sample<POSE, VIEW, DEG>(g, op, ray, Y, GY, s, Chat, Dhat, gC, gDr, st,
+                have = backward_sample<POSE, VIEW, DEG, true>(g, op, ray, Y, GY, s, Chat, Dhat, gC, gDr, st,
                                                    pa, idx, w, gsig, gs);
             scatter_merged<DEG, FIX>(have, s.base, idx, w, gsig, gs, Y, wc, grad);
             ++k;
@@ -323,7 +326,7 @@ __device__ __forceinline__ void ray_backward(const KGrid& g, const KOpts& op, co
             int idx[8];
             float w[8];
             float gsig, gs[3];
-            backward_sample<POSE, VIEW, DEG>(g, op, ray, Y, GY, s, Chat, Dhat, gC, gDr, st, pa, idx, w,
+            backward_sample<POSE, VIEW, DEG, false>(g, op, ray, Y, GY, s, Chat, Dhat, gC, gDr, st, pa, idx, w,
                                         gsig, gs);
         }
     } else {
@@ -348,7 +351,7 @@ __device__ __forceinline__ void ray_backward(const KGrid& g, const KOpts& op, co
             int idx[8];
             float w[8];
             float gsig, gs[3];
-            backward_sample<POSE, VIEW, DEG>(g, op, ray, Y, GY, s, Chat, Dhat, gC, gDr, st, pa, idx, w,
+            backward_sample<POSE, VIEW, DEG, true>(g, op, ray, Y, GY, s, Chat, Dhat, gC, gDr, st, pa, idx, w,
                                         gsig, gs);
             ++k;
         }

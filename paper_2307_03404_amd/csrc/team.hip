@@ -441,6 +441,7 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
                 bool have = false;
                 if (work) {
                     have = load_links(g, s.base, idx) > 0;
+                    if (have && g.probe) have = gather_density<DEG>(g, idx, s.f) > 0.f;
                     if (have) gather_interp<POSE_HERE, POSE_HERE && VIEW, DEG>(g, idx, Y, GY, s.f, v);
                 }
                 Lit q;
