@@ -169,6 +169,7 @@ struct Lit {
 struct Carry {
     double L;
     double A[3], AD;
+    float T;            // transmittance behind L; kept by teams of one only
 };
 
 // Optical depth of the window's samples (sr <= 0 or NaN: no light), their
@@ -181,8 +182,8 @@ __device__ __forceinline__ void composite(const KOpts& op, const Team& tm, bool 
     q.lit = have && sr > 0.f;
     const float x = q.lit ? sr * op.step_vox : 0.f;
     const double Li = cy.L + team_scan((double)x, tm);
-    const float Tb = trans_of(team_prev(Li, cy.L, tm));
-    q.Tn = trans_of(Li);
+    const float Tb = tm.T == 1 ? cy.T : trans_of(team_prev(Li, cy.L, tm));
+    q.Tn = cy.T = trans_of(Li);
     last = WAVE;
     if (STOPS) {
         const unsigned long long m = __ballot(q.lit && q.Tn < op.t_stop) & tm.mask;
@@ -400,7 +401,7 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
             for (int k = 0; k < (VIEW ? 3 : 1); ++k) ps.V[k][a] = 0.f;
         }
     }
-    Carry cy = {0.0, {0.0, 0.0, 0.0}, 0.0};
+    Carry cy = {0.0, {0.0, 0.0, 0.0}, 0.0, 1.f};
     int64_t kept = 0;                                       // kept sample positions of the ray
     int windows = 0;                                        // kept windows (the same on the whole wave)
     bool spilled = false;
@@ -580,7 +581,7 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
         }
     }
     if (KEEP) {
-        cy = Carry{0.0, {0.0, 0.0, 0.0}, 0.0};
+        cy = Carry{0.0, {0.0, 0.0, 0.0}, 0.0, 1.f};
         for (int b = 0; b < windows; ++b) {
             const int32_t at = keep_at[b * WAVE];
             const bool have = valid && at >= 0;
