@@ -291,6 +291,24 @@ int pxm_grid_rmsprop(int64_t n_alloc, int32_t sh_degree, float *data, float *gra
                      void *stream);
 
 /*
+ * The ray batch of a mapping iteration (Sec. 5.4, 6.1): n_rays keyframe rays,
+ * given by ascending indices into the keyframes' rays (repeats allowed), with
+ * their targets, the CSR offsets of the n_frames keyframes they come from and
+ * the loss weight 1 / max(1, M) of each frame, M the rays of the batch whose
+ * target depth is finite and > 0.
+ *   index         [n_rays] int64, ascending; a value outside [0, n_kf) reads the
+ *                 nearest ray inside, so it cannot lead out of bounds
+ *   kf_offsets    [F+1] CSR of the n_kf keyframe rays (n_kf >= 1 when n_rays > 0),
+ *                 kf_pix [n_kf][2], kf_rgb [n_kf][3], kf_depth [n_kf]
+ *   pix [n_rays][2], rgb [n_rays][3], depth [n_rays], frame_offsets [F+1],
+ *   frame_weight [F]: written
+ */
+int pxm_gather_rays(int64_t n_rays, const int64_t *index, int64_t n_kf, int32_t n_frames,
+                    const int32_t *kf_offsets, const int32_t *kf_pix, const float *kf_rgb,
+                    const float *kf_depth, int32_t *pix, float *rgb, float *depth,
+                    int32_t *frame_offsets, float *frame_weight, void *stream);
+
+/*
  * Occupancy bitfield for empty-space skipping (an exact acceleration: a cell
  * whose 8 corners are all empty interpolates to zero density and carries no
  * light or gradient).  Level 0 holds one 64-bit word per block of 4^3 cells,

@@ -266,6 +266,10 @@ class MappingLoop:
         n_all = int(kf.pix.shape[0])
         if indices is None:
             indices = torch.randint(0, n_all, (self.n_rays,), device=dev, generator=self.gen)
+            if self._plain():
+                # indices known to be good: one launch, nothing waits for the device
+                idx = torch.sort(indices).values
+                return idx, *pxm.gather_rays(idx, kf, self.tgt_rgb, self.tgt_depth)
         idx = torch.sort(indices).values
         fid = self._frame_ids[idx]
         F = kf.c2w.shape[0]
@@ -278,6 +282,14 @@ class MappingLoop:
         valid = torch.isfinite(depth) & (depth > 0)
         w = (1.0 / valid.sum().clamp(min=1).to(torch.float32)).expand(F).contiguous()
         return idx, rays, rgb, depth, w
+
+    def _plain(self):
+        """Keyframe rays and targets as pxm.gather_rays reads them."""
+        kf = self.kf
+        n, F = int(kf.pix.shape[0]), int(kf.c2w.shape[0])
+        return all(t.is_cuda and t.is_contiguous() and t.dtype == dt and tuple(t.shape) == shape for t, dt, shape in (
+            (kf.pix, torch.int32, (n, 2)), (kf.frame_offsets, torch.int32, (F + 1,)),
+            (self.tgt_rgb, torch.float32, (n, 3)), (self.tgt_depth, torch.float32, (n,))))
 
     def grow(self):
         """Coarse-to-fine growth of the map (Sec. 6.1's dynamic grid; see

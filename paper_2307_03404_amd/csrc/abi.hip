@@ -351,6 +351,23 @@ int pxm_grid_rmsprop(int64_t n_alloc, int32_t sh_degree, float* data, float* gra
                                         alpha, eps, (hipStream_t)stream), "grid_rmsprop");
 }
 
+int pxm_gather_rays(int64_t n_rays, const int64_t* index, int64_t n_kf, int32_t n_frames,
+                    const int32_t* kf_offsets, const int32_t* kf_pix, const float* kf_rgb,
+                    const float* kf_depth, int32_t* pix, float* rgb, float* depth,
+                    int32_t* frame_offsets, float* frame_weight, void* stream) {
+    if (n_rays < 0 || n_kf < 0) return fail(PXM_INVALID_ARGUMENT, "n_rays or n_kf < 0");
+    if (n_rays > INT32_MAX) return fail(PXM_UNSUPPORTED, "n_rays beyond int32 offsets");
+    if (n_frames < 1) return fail(PXM_INVALID_ARGUMENT, "n_frames < 1");
+    if (!kf_offsets || !frame_offsets || !frame_weight)
+        return fail(PXM_INVALID_ARGUMENT, "offsets / frame_weight is NULL");
+    if (n_rays > 0 && n_kf < 1) return fail(PXM_INVALID_ARGUMENT, "n_kf < 1");
+    if (n_rays > 0 && (!index || !kf_pix || !kf_rgb || !kf_depth || !pix || !rgb || !depth))
+        return fail(PXM_INVALID_ARGUMENT, "a required array is NULL");
+    return launched(pxm::launch_gather_rays(n_rays, index, n_kf, n_frames, kf_offsets, kf_pix, kf_rgb,
+                                            kf_depth, pix, rgb, depth, frame_offsets, frame_weight,
+                                            (hipStream_t)stream), "gather_rays");
+}
+
 size_t pxm_grid_edit_workspace_bytes(const pxm_grid* grid) {
     if (check_grid(grid, false) != PXM_OK) return 0;
     const size_t up = pxm::grow_workspace_bytes(grid->reso);

@@ -107,6 +107,10 @@ hipError_t launch_pose_gn(int F, float* c2w, double* gn, float mu, hipStream_t s
 hipError_t launch_rmsprop(int64_t n, int deg, float* data, float* grad, float* avg, float lr_d,
                           float lr_sh, float alpha, float eps, hipStream_t st);
 
+hipError_t launch_gather_rays(int64_t n, const int64_t* index, int64_t n_kf, int F, const int32_t* kf_off, const int32_t* kf_pix,
+                              const float* kf_rgb, const float* kf_depth, int32_t* pix, float* rgb, float* depth,
+                              int32_t* off, float* weight, hipStream_t st);
+
 // Dynamic-grid edits: flags are compacted in chunks of EDIT_CHUNK items
 // (one workgroup).  Workspace bytes of a prune of n_alloc records and of the
 // growth of an R[0] x R[1] x R[2] lattice.

@@ -65,4 +65,67 @@ hipError_t launch_rmsprop(int64_t n, int deg, float* data, float* grad, float* a
     return hipGetLastError();
 }
 
+// Ray batch of a mapping iteration, in one launch: workgroup 0 counts the valid
+// target depths and finds the frames' offsets (the indices ascend, so frame f
+// starts at the first index that is not below its keyframe offset); the others
+// copy a ray per lane.  13 launches of elementwise and index kernels and a
+// host synchronisation before.
+constexpr int COUNT_THREADS = 1024;
+
+__global__ void __launch_bounds__(COUNT_THREADS) k_gather_rays(int64_t n, const int64_t* __restrict__ index, int64_t n_kf, int F,
+                                                               const int32_t* __restrict__ kf_off,
+                                                               const int32_t* __restrict__ kf_pix,
+                                                               const float* __restrict__ kf_rgb,
+                                                               const float* __restrict__ kf_depth,
+                                                               int32_t* __restrict__ pix, float* __restrict__ rgb,
+                                                               float* __restrict__ depth, int32_t* __restrict__ off,
+                                                               float* __restrict__ weight) {
+    auto ray = [&](int64_t r) -> int64_t {
+        const int64_t i = index[r];
+        return i < 0 ? 0 : i >= n_kf ? n_kf - 1 : i;
+    };
+    if (blockIdx.x > 0) {
+        const int64_t r = (int64_t)(blockIdx.x - 1) * COUNT_THREADS + threadIdx.x;
+        if (r >= n) return;
+        const int64_t i = ray(r);
+        pix[2 * r] = kf_pix[2 * i];
+        pix[2 * r + 1] = kf_pix[2 * i + 1];
+        rgb[3 * r] = kf_rgb[3 * i];
+        rgb[3 * r + 1] = kf_rgb[3 * i + 1];
+        rgb[3 * r + 2] = kf_rgb[3 * i + 2];
+        depth[r] = kf_depth[i];
+        return;
+    }
+    __shared__ long long s_count[COUNT_THREADS / WAVE];
+    long long count = 0;
+    for (int64_t r = threadIdx.x; r < n; r += COUNT_THREADS) {
+        const float d = kf_depth[ray(r)];
+        count += isfinite(d) && d > 0.f;
+    }
+    count = wave_sum(count);
+    if (lane_id() == 0) s_count[threadIdx.x / WAVE] = count;
+    __syncthreads();
+    count = 0;
+    for (int w = 0; w < COUNT_THREADS / WAVE; ++w) count += s_count[w];
+    const float m = 1.0f / (float)(count < 1 ? 1 : count);
+    for (int f = threadIdx.x; f <= F; f += COUNT_THREADS) {
+        int64_t lo = 0, hi = n;                             // first r with ray(r) >= kf_off[f]
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) / 2;
+            if (ray(mid) < kf_off[f]) lo = mid + 1; else hi = mid;
+        }
+        off[f] = (int32_t)(f == 0 ? 0 : f == F ? n : lo);
+        if (f < F) weight[f] = m;
+    }
+}
+
+hipError_t launch_gather_rays(int64_t n, const int64_t* index, int64_t n_kf, int F, const int32_t* kf_off, const int32_t* kf_pix,
+                              const float* kf_rgb, const float* kf_depth, int32_t* pix, float* rgb, float* depth,
+                              int32_t* off, float* weight, hipStream_t st) {
+    const unsigned blocks = 1 + (unsigned)((n + COUNT_THREADS - 1) / COUNT_THREADS);
+    hipLaunchKernelGGL(k_gather_rays, dim3(blocks), dim3(COUNT_THREADS), 0, st, n, index, n_kf, F, kf_off, kf_pix, kf_rgb,
+                       kf_depth, pix, rgb, depth, off, weight);
+    return hipGetLastError();
+}
+
 }  // namespace pxm

@@ -62,7 +62,7 @@ _lib = None
 _lock = threading.Lock()
 EXPORTS = ("pxm_render_forward", "pxm_render_backward_grid", "pxm_render_backward_pose",
            "pxm_tv_grad", "pxm_tv_grad_set", "pxm_render_fused", "pxm_render_fused_noalloc",
-           "pxm_pose_adam", "pxm_grid_rmsprop", "pxm_render_gn", "pxm_pose_gn",
+           "pxm_pose_adam", "pxm_grid_rmsprop", "pxm_gather_rays", "pxm_render_gn", "pxm_pose_gn",
            "pxm_grid_edit_workspace_bytes", "pxm_grid_upsample_link", "pxm_grid_upsample_data",
            "pxm_probe_read_bandwidth",
            "pxm_grid_prune",
@@ -95,6 +95,8 @@ def lib():
         L.pxm_render_fused_noalloc.argtypes = [G, R, O, P, P, P, i32, P, P, P, P, P, P, P]
         L.pxm_pose_adam.argtypes = [i32, P, P, P, f32, f32, f32, f32, P]
         L.pxm_grid_rmsprop.argtypes = [i64, i32, P, P, P, f32, f32, f32, f32, P]
+        L.pxm_gather_rays.argtypes = [i64, P, i64, i32, P, P, P, P, P, P, P, P, P, P]
+        L.pxm_gather_rays.restype = C.c_int
         L.pxm_render_gn.argtypes = [G, R, O, P, P, P, P, P]
         L.pxm_pose_gn.argtypes = [i32, P, P, f32, P]
         L.pxm_probe_read_bandwidth.argtypes = [P, sz, i32, P, sz, P]
@@ -473,6 +475,27 @@ def grid_rmsprop(data, grad_data, state, lr_density, lr_sh, alpha=0.95, eps=1e-8
     _check("grid_rmsprop", lib().pxm_grid_rmsprop(n, int(sh_degree), _ptr(data), _ptr(grad_data), _ptr(state),
                                                   float(lr_density), float(lr_sh), float(alpha),
                                                   float(eps), _stream(stream)))
+
+
+def gather_rays(index, keyframes: DeviceRays, kf_rgb, kf_depth, stream=None):
+    """The batch of keyframe rays `index` (int64, ascending, repeats allowed):
+    (rays, rgb, depth, frame_weight) with the weight 1 / (valid depths of the
+    batch) in every frame (pxm_gather_rays)."""
+    n, F, n_kf = int(index.shape[0]), keyframes.n_frames, keyframes.n_rays
+    dev = index.device
+    _need(index, "index", torch.int64, (n,))
+    _need(keyframes.frame_offsets, "keyframes.frame_offsets", torch.int32, (F + 1,))
+    _need(keyframes.pix, "keyframes.pix", torch.int32, (n_kf, 2))
+    _need(kf_rgb, "kf_rgb", torch.float32, (n_kf, 3))
+    _need(kf_depth, "kf_depth", torch.float32, (n_kf,))
+    pix = torch.empty(n, 2, dtype=torch.int32, device=dev)
+    off = torch.empty(F + 1, dtype=torch.int32, device=dev)
+    rgb, depth = torch.empty(n, 3, device=dev), torch.empty(n, device=dev)
+    weight = torch.empty(F, device=dev)
+    _check("gather_rays", lib().pxm_gather_rays(
+        n, _ptr(index), n_kf, F, _ptr(keyframes.frame_offsets), _ptr(keyframes.pix), _ptr(kf_rgb),
+        _ptr(kf_depth), _ptr(pix), _ptr(rgb), _ptr(depth), _ptr(off), _ptr(weight), _stream(stream)))
+    return DeviceRays(keyframes.c2w, keyframes.intr, off, pix), rgb, depth, weight
 
 
 # ----------------------------------------------------------------------------
