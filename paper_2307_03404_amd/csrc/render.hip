@@ -237,14 +237,59 @@ __device__ __forceinline__ int next_mark(const uint32_t* marks, int last, int o)
     return w * 32 + __ffs(b) - 1;
 }
 
+// Which lanes of a wave take part in a step of the grid backward.  The wave
+// stands at its lanes' smallest pending sample index, and as a rule the lanes
+// at that index work (neighbouring rays then share cells, and a cell's
+// gradient is added once for all of them).  Rays of a sparse pixel subset share
+// few cells, and their samples lie at so many indices that a step finds a
+// handful of lanes: the steps then number the union of the lanes' indices.  So
+// each wave counts what its steps have merged, and once that is less than half
+// (MERGED_FEW) of what could have been, a step that holds less than half of the
+// pending lanes (FIRST_FEW) takes all of them instead, each at its own next
+// index.  512^3 room, 16 frames of 30k rays each: fused step 4.58 -> 3.62 ms,
+// backward alone 4.98 -> 4.27.  Always taking all is slower where rays do share
+// cells (8 frames of 50k rays of the 256^3 room 2.91 ms in step, 3.19 always
+// all, 2.81 by this rule; 8 full frames of the 512^3 room 17.4, 18.4, 17.4);
+// rules of a quarter and an eighth merged give up part of the gain (4.03, 4.19).
+// The fixed-point scatter keeps to the common index: its rounding, and so its
+// bits, follow what is merged.
+constexpr int MERGED_FEW = 2, FIRST_FEW = 2;
+constexpr int MERGE_EVIDENCE = 16;                          // lanes that could have merged before it counts
+
+// The wave's next index after k: nothing pending is below k + 1, where as a rule
+// some lane stands; the reduction is for the others (backward of that frame 841
+// -> 822 us, of 8 frames of the 512^3 room 14.7 -> 14.3 ms).
+__device__ __forceinline__ int64_t next_step(int64_t k, int64_t mine) {
+    return __ballot(mine == k + 1) ? k + 1 : wave_min(mine);
+}
+
+struct StepRule {
+    int could = 0, did = 0;                                 // lanes beyond each step's first; of them merged
+
+    __device__ __forceinline__ bool takes_part(bool pending, bool first) const {
+        const bool apart = could >= MERGE_EVIDENCE && did * MERGED_FEW < could;
+        if (!apart || (int)__popcll(__ballot(first)) * FIRST_FEW >= (int)__popcll(__ballot(pending))) return first;
+        return pending;
+    }
+
+    __device__ __forceinline__ void count(bool have, int cells) {
+        const int n = (int)__popcll(__ballot(have));
+        if (n) {
+            could += n - 1;
+            did += n - cells;
+        }
+    }
+};
+
 // Backward march of one ray over its first n kept positions (Eq. 6-14).
 //   Chat, Dhat: the forward's colour and expected range
 //   gC, gDr:    dL/dC-hat and dL/d(range)
-// With GRID the lanes of a wave march in lockstep on the absolute sample
-// index (so that lanes of one tile share cells and their scatters merge):
-// every lane must call this (lanes without a ray pass n = 0); steps where no
-// lane has an occupied cell are jumped over together.  Without GRID every
-// lane marches on its own.
+// With GRID the lanes of a wave work together in steps (StepRule), so that the
+// scatters of rays that share cells merge: every lane must call this (lanes
+// without a ray pass n = 0).  Each lane looks up its own next work position; a
+// common walk over the indices at which any lane has one took 987 us where this
+// takes 822 (backward of a 1200 x 680 frame of the 256^3 room).  Without GRID
+// every lane marches on its own.
 template <bool GRID, bool POSE, bool VIEW, int DEG, bool FIX = false>
 __device__ __forceinline__ void ray_backward(const KGrid& g, const KOpts& op, const Ray& ray,
                                              const float Y[9], int n, const double Chat[3],
@@ -257,56 +302,50 @@ __device__ __forceinline__ void ray_backward(const KGrid& g, const KOpts& op, co
     BwdState st = {{0.0, 0.0, 0.0}, 0.0, 1.f, 0.0};
     const int64_t ks = ray.k_first, ke = ray.k_first + (n > 0 ? n : 0);
     bool has = n > 0;
+    StepRule rule;
     if (GRID && marks && __ballot(mark_overflow && n > 0) == 0) {
-        // the forward of this kernel marked every work position: visit only
-        // those, the wave at the smallest pending one
+        // the forward of this kernel marked every work position: visit only those
         int off = has ? next_mark(marks, mark_last, 0) : -1;
-        for (;;) {
-            const int64_t mine = off >= 0 ? ks + off : INT64_MAX;
-            const int64_t k = wave_min(mine);
-            if (k == INT64_MAX) break;
-            const bool work = mine == k;
+        int64_t mine = off >= 0 ? ks + off : INT64_MAX;
+        for (int64_t k = wave_min(mine); k != INT64_MAX; k = next_step(k, mine)) {
+            const bool pending = off >= 0;
+            const bool work = FIX ? mine == k : rule.takes_part(pending, mine == k);
             bool have = false;
             int idx[8];
             float w[8];
             float gsig = 0.f, gs[3] = {0.f, 0.f, 0.f};
             Sample s;
-            if (work && sample_at(g, ray, k, s))
+            if (work && sample_at(g, ray, mine, s))
                 have = backward_sample<POSE, VIEW, DEG, false>(g, op, ray, Y, GY, s, Chat, Dhat, gC, gDr, st,
                                                    pa, idx, w, gsig, gs);
-            scatter_merged<DEG, FIX>(have, s.base, idx, w, gsig, gs, Y, wc, grad);
-            if (work) off = next_mark(marks, mark_last, off + 1);
+            rule.count(have, scatter_merged<DEG, FIX>(have, s.base, idx, w, gsig, gs, Y, wc, grad));
+            if (work) {
+                off = next_mark(marks, mark_last, off + 1);
+                mine = off >= 0 ? ks + off : INT64_MAX;
+            }
         }
     } else if (GRID) {
-        int64_t k = wave_min(has ? ks : INT64_MAX);
+        // each lane looks up its own next position in an occupied cell
+        int64_t pos = ks;
+        Sample s;
         OccCache oc;
         occ_cache_init(oc);
-        for (;;) {
-            const bool live = has && k < ke;
-            if (__ballot(live) == 0) break;
-            const bool run = live && k >= ks;
-            int64_t adv = live ? (run ? 1 : ks - k) : INT64_MAX;
-            bool work = false;
-            Sample s;
-            if (run) {
-                if (!sample_at(g, ray, k, s)) {
-                    has = false;            // left the box: nothing further on this ray
-                    adv = INT64_MAX;
-                } else if (!g.occ0) {
-                    work = true;
-                } else {
-                    int64_t nxt;
-                    const int cls = occ_classify(g, ray, k, s.c, oc, nxt);
-                    if (cls == OCC_JUMP) adv = (nxt < ke ? nxt : ke) - k;
-                    else work = cls == OCC_CELL;
-                }
+        auto seek = [&]() {
+            while (pos < ke) {
+                if (!sample_at(g, ray, pos, s)) return false;   // left the box: nothing further on this ray
+                if (!g.occ0) return true;
+                int64_t nxt;
+                const int cls = occ_classify(g, ray, pos, s.c, oc, nxt);
+                if (cls == OCC_CELL) return true;
+                pos = cls == OCC_JUMP ? (nxt < ke ? nxt : ke) : pos + 1;
             }
-            if (__ballot(work) == 0) {
-                const int64_t step = wave_min(adv);
-                if (step == INT64_MAX) break;       // every live lane has just left the box
-                k += step;
-                continue;
-            }
+            return false;
+        };
+        int64_t mine = has && seek() ? pos : INT64_MAX;
+        for (int64_t k = wave_min(mine); k != INT64_MAX; k = next_step(k, mine)) {
+            const bool pending = mine != INT64_MAX;
+            const bool first = mine == k;
+            const bool work = FIX ? first : rule.takes_part(pending, first);
             bool have = false;
             int idx[8];
             float w[8];
@@ -314,8 +353,11 @@ __device__ __forceinline__ void ray_backward(const KGrid& g, const KOpts& op, co
             if (work)
                 have = backward_sample<POSE, VIEW, DEG, true>(g, op, ray, Y, GY, s, Chat, Dhat, gC, gDr, st,
                                                    pa, idx, w, gsig, gs);
-            scatter_merged<DEG, FIX>(have, s.base, idx, w, gsig, gs, Y, wc, grad);
-            ++k;
+            rule.count(have, scatter_merged<DEG, FIX>(have, s.base, idx, w, gsig, gs, Y, wc, grad));
+            if (work) {
+                ++pos;
+                mine = seek() ? pos : INT64_MAX;
+            }
         }
     } else if (marks && !mark_overflow) {
         // per lane: straight from one marked position to the next
@@ -397,7 +439,7 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2, 2)
                                                   const float* __restrict__ g_depth,
                                                   float* __restrict__ grad) {
     extern __shared__ float smem[];
-    const WaveStage wc = wave_stage(smem);
+    const WaveStage wc = wave_stage(smem, grad, (uint64_t)g.n_alloc * (RecL<DEG>::S * sizeof(float)));
     const int64_t r = ray_tile(blockIdx.x, gridDim.x) * WAVE + threadIdx.x;
     bool active = r < rs.n;
     Ray ray;
@@ -448,9 +490,9 @@ __global__ void __launch_bounds__(256, (PH == 1 ? 4 : 1)) k_fused(KGrid g, KRays
                                                KSplit sp) {
     __shared__ int64_t s_tile;
     extern __shared__ float smem[];
-    WaveStage wc{nullptr, nullptr, nullptr, nullptr};
+    WaveStage wc{};
     if (GRID && PH != 1) {
-        wc = wave_stage(smem);
+        wc = wave_stage(smem, grad, (uint64_t)g.n_alloc * (RecL<DEG>::S * sizeof(float)));
         wc.gfix = sp.gfix;
     }
     const int64_t n_tiles = (rs.n + blockDim.x - 1) / blockDim.x;

@@ -338,8 +338,8 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
     constexpr bool ONE_MARCH = POSE && MODE == TEAM_FUSED;  // pose sums of the compositing march
     constexpr bool KEEP = (GRID && MODE == TEAM_FUSED) || GAUSS_NEWTON;   // windows kept for the second pass
     extern __shared__ float smem[];
-    WaveStage wc{nullptr, nullptr, nullptr, nullptr};
-    if (GRID) wc = wave_stage(smem);
+    WaveStage wc{};
+    if (GRID) wc = wave_stage(smem, io.grad, (uint64_t)g.n_alloc * (RecL<DEG>::S * sizeof(float)));
     const int lane = lane_id();
     constexpr int KEPT = GAUSS_NEWTON ? GN_WINDOWS : GRID_WINDOWS;
     float4* keep = reinterpret_cast<float4*>(wc.marks) + lane;
