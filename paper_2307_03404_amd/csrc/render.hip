@@ -429,10 +429,13 @@ __global__ void __launch_bounds__(FORWARD_RAYS) k_forward(KGrid g, KRays rs, KOp
     nsamp[r] = fr.n;
 }
 
-// Its LDS holds 2 waves on a SIMD; told so, the compiler takes the registers they
-// leave (1003 against 1065 us for 226,730 rays).
+// It keeps no work masks, so its LDS (the staging alone) holds 13 waves on a CU,
+// and its 168 registers 3 on a SIMD.  With the mask region allocated, and so 2,
+// the backward of a 1200 x 680 frame of the 256^3 room took 827 us and takes 762,
+// of 8 frames of the 512^3 room 14.2 and 11.7 ms, of a frame of the 32^3 map 467
+// and 372 us.
 template <int DEG>
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2, 2))) k_backward(KGrid g, KRays rs, KOpts op,
+__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(3, 3))) k_backward(KGrid g, KRays rs, KOpts op,
                                                   const float* __restrict__ rgb,
                                                   const float* __restrict__ depth,
                                                   const int32_t* __restrict__ nsamp,
@@ -684,9 +687,9 @@ hipError_t launch_backward(const KGrid& g, const KRays& rs, const KOpts& op, con
     if (lt > 0 || grad_pose)
         return team_backward(g, rs, op, lt, rgb, depth, nsamp, g_rgb, g_depth, grad_data, grad_pose, st);
     by_degree(g.deg, [&](auto D) {
-        // one wave per workgroup: each wave stages its MFMA operands in ~19 KB of LDS
+        // one wave per workgroup: each wave stages its MFMA operands in 11.5 KB of LDS
         hipLaunchKernelGGL((k_backward<decltype(D)::value>), dim3(blocks_for(rs.n, WAVE)), dim3(WAVE),
-                           WAVE_LDS_FLOATS * sizeof(float), st, g, rs, op, rgb, depth, nsamp, g_rgb, g_depth, grad_data);
+                           STAGE_LDS_FLOATS * sizeof(float), st, g, rs, op, rgb, depth, nsamp, g_rgb, g_depth, grad_data);
     });
     return hipGetLastError();
 }

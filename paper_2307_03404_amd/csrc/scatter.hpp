@@ -32,7 +32,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int STAGE_LD = 33;                              // padded row: conflict-free reads
 constexpr int STAGE_FLOATS = 2 * REC * STAGE_LD;          // G: rows h * REC + i
 constexpr int MARK_WORDS = 32;                            // work-position mask: 1024 bits per lane
-constexpr int WAVE_LDS_FLOATS = STAGE_FLOATS + 2 * WAVE * 8 + MARK_WORDS * WAVE;
+constexpr int STAGE_LDS_FLOATS = STAGE_FLOATS + 2 * WAVE * 8;
+constexpr int WAVE_LDS_FLOATS = STAGE_LDS_FLOATS + MARK_WORDS * WAVE;   // the marks are last: a kernel without them takes less
 
 // Byte offset of no record: past the end of every gradient array that is
 // addressed by offsets (a buffer store or atomic there does nothing), also with
