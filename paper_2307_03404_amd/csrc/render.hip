@@ -777,7 +777,15 @@ hipError_t launch_fused(const KGrid& g, const KRays& rs, const KOpts& op, const 
     // for the pose alone at every size); the counters and the fixed-point
     // scatter, whose result does not depend on the launch form, stay with one
     const int lt = team_lanes_log2(rs.n, want);
-    if (variant == 0 && !gfix && !(want & 4) && (lt > 0 || (want & 3) == 2))
+    // The pose alone, many rays, on a dense map: one lane per ray in two marches
+    // reads less than a team in one, as its first march ends at a sample's
+    // densities and its second visits only the lit ones (32^3 map, us: 12 frames
+    // of 16k rays 387 against 360 with teams of two, of 20k 417 and 424, of 30k 480
+    // and 543, of 50k 632 and 834).  On sparse maps the densities are read with the
+    // rest, and the team wins at every size (256^3 room: 12 frames of 30k 1100 and
+    // 988, of 50k 1400 and 1332).
+    const bool alone = (want & 3) == 2 && g.probe && rs.n > 200000;
+    if (variant == 0 && !alone && !gfix && !(want & 4) && (lt > 0 || (want & 3) == 2))
         return team_fused(g, rs, op, lt, tgt_rgb, tgt_depth, frame_weight, want, rgb, depth, loss, grad_data, grad_pose, st);
     // a wave works alone: workgroups of one wave leave no registers and LDS with
     // waves that wait for the slowest of four (64 uneven frames of the 512^3

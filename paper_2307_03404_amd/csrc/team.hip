@@ -733,14 +733,19 @@ static void team_deg(const KGrid& g, const KRays& rs, const KOpts& op, int log_t
 //                19,200 rays  -782 | 916 469 301 228 179 194 251
 //               163,200 rays  -787 | 1002 781 834
 //               816,000 rays -1419 | 1914 2061
+// Two lanes for the pose alone stay ahead up to 400,000 rays (PAIRS), with four
+// or more lanes' limit as before; fused pose step and backward of the pose, us,
+// one lane and two: a frame of 360,150 rays of the 256^3 room 964 -> 851 and 756
+// -> 591, 12 sparse frames of 30k 1111 -> 988 and 841 -> 720, of the 32^3 map 465
+// -> 398 (backward); a frame of 576,000 989 -> 1071 and 703 -> 712.
 // The one-lane kernels stay where they are faster: forward and grid gradients of
 // large batches, which this returns 0 for.
 int team_lanes_log2(int64_t n_rays, int want) {
-    constexpr int64_t MANY = 5300, RESIDENT = 2700;
+    constexpr int64_t PAIRS = 12500, MANY = 5300, RESIDENT = 2700;
     const bool grid = want & 1, pose = want & 2;
     const int narrow = grid ? 4 : pose ? 1 : 6;
     int lt = 0;
-    while (lt < 6 && (n_rays << (lt + 1)) <= WAVE * (lt + 1 <= narrow ? MANY : RESIDENT)) ++lt;
+    while (lt < 6 && (n_rays << (lt + 1)) <= WAVE * (lt + 1 > narrow ? RESIDENT : grid || !pose ? MANY : PAIRS)) ++lt;
     return lt;
 }
 

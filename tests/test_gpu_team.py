@@ -80,3 +80,10 @@ def test_more_lit_windows_than_are_kept(n):
     data[:, 0] = rng.uniform(0.01, 0.2, size=data.shape[0])
     opts = dataclasses.replace(wl.opts, step_vox=synth.f32(0.05 if n == 40 else 0.1), max_samples=2 ** 31 - 1)
     _check(wl.replace(grid=dataclasses.replace(wl.grid, data=data), opts=opts))
+
+
+# the pose alone: two lanes per ray up to 400,000 rays; on a map that is mostly
+# allocated (this one) one lane from 200,001 on
+@pytest.mark.parametrize("n", [200000, 200001])
+def test_pose_alone_of_many_rays_on_a_dense_map(n):
+    _check(synth.subset_rays(synth.config3(), n, seed=n))
