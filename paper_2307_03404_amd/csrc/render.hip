@@ -774,7 +774,7 @@ hipError_t launch_fused(const KGrid& g, const KRays& rs, const KOpts& op, const 
                         int64_t* stats, unsigned* ws, int block, int variant,
                         unsigned long long* gfix, hipStream_t st) {
     // variant 0 takes a team of lanes per ray where that is faster (team_lanes_log2;
-    // for the pose alone at every size); the counters and the fixed-point
+    // for the pose alone also of one lane, which needs one march only); the counters and the fixed-point
     // scatter, whose result does not depend on the launch form, stay with one
     const int lt = team_lanes_log2(rs.n, want);
     // The pose alone, many rays, on a dense map: one lane per ray in two marches
