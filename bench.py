@@ -291,7 +291,7 @@ def tracking_bench(wl, g, r, trgb, tdep, fw, args):
     block, variant = pxm.get_tuning()
     kname = ("k_team (Gauss-Newton)" if args.gauss_newton
              else "k_fused<false,true,false,1> + k_fused<false,true,false,2>"
-             if variant == 2 else "k_fused<false,true,false,0>" if variant == 1 else "k_team (pose)")
+             if variant == 2 else "k_fused<false,true,false,0>")
     traffic = None if args.gauss_newton else measured_traffic(wl.name, block, variant)
     what = ("fwd + residual + 4x6 pose Jacobian + per-frame normal equations + damped "
             "Gauss-Newton step" if args.gauss_newton else "fwd + loss + se(3) pose bwd + Adam")
