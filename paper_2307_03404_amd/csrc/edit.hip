@@ -316,22 +316,21 @@ __global__ __launch_bounds__(EDIT_THREADS) void k_fine_link(Lattice L, const uin
 
 // Component c of the eight fine records: sums over corners in (x, y, z) bit order,
 // an empty corner 0, in FP64, scaled by their power of two at the end (which
-// rounds as scaling each term would) and rounded once to FP32.  A sum of two
-// is the FP32 sum: rounding it to 53 bits first changes nothing.  Sums share
-// their common beginnings.
+// rounds as scaling each term would) and rounded once to FP32.  Pairs too: an
+// FP32 sum of two overflows before its scale brings it back, and rounds twice
+// where the scaled value is subnormal.  Sums share their common beginnings.
 __device__ __forceinline__ void fine_values(const float v[8][4], int c, float scale, float r[8][4]) {
-    const float z = 0.f + v[0][c];                          // a sum starts at +0
-    const float h = 0.5f * scale;
-    const double q = 0.25 * (double)scale, e = 0.125 * (double)scale;
+    const double h = 0.5 * (double)scale, q = 0.25 * (double)scale, e = 0.125 * (double)scale;
     double d[8];
 #pragma unroll
     for (int b = 0; b < 8; ++b) d[b] = (double)v[b][c];
-    const double s0 = (double)z, s01 = s0 + d[1], s3 = s01 + d[2] + d[3];
-    r[0][c] = z * scale;
-    r[1][c] = (z + v[1][c]) * h;
-    r[2][c] = (z + v[2][c]) * h;
+    const double s0 = 0.0 + d[0];                           // a sum starts at +0
+    const double s01 = s0 + d[1], s3 = s01 + d[2] + d[3];
+    r[0][c] = (float)(s0 * (double)scale);
+    r[1][c] = (float)(s01 * h);
+    r[2][c] = (float)((s0 + d[2]) * h);
     r[3][c] = (float)(s3 * q);
-    r[4][c] = (z + v[4][c]) * h;
+    r[4][c] = (float)((s0 + d[4]) * h);
     r[5][c] = (float)((s01 + d[4] + d[5]) * q);
     r[6][c] = (float)((s0 + d[2] + d[4] + d[6]) * q);
     r[7][c] = (float)((s3 + d[4] + d[5] + d[6] + d[7]) * e);
