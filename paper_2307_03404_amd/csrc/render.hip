@@ -442,7 +442,7 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(3, 3)
                                                   const float* __restrict__ g_rgb,
                                                   const float* __restrict__ g_depth,
                                                   float* __restrict__ grad) {
-    extern __shared__ float smem[];
+    extern __shared__ __align__(16) float smem[];
     const WaveStage wc = wave_stage(smem, grad, (uint64_t)g.n_alloc * (RecL<DEG>::S * sizeof(float)));
     const int64_t r = ray_tile(blockIdx.x, gridDim.x) * WAVE + threadIdx.x;
     bool active = r < rs.n;
@@ -493,7 +493,7 @@ __global__ void __launch_bounds__(256, (PH == 1 ? 4 : 1)) k_fused(KGrid g, KRays
                                                unsigned* __restrict__ ws, int persistent,
                                                KSplit sp) {
     __shared__ int64_t s_tile;
-    extern __shared__ float smem[];
+    extern __shared__ __align__(16) float smem[];
     WaveStage wc{};
     if (GRID && PH != 1) {
         wc = wave_stage(smem, grad, (uint64_t)g.n_alloc * (RecL<DEG>::S * sizeof(float)));

@@ -337,7 +337,7 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
     constexpr bool GAUSS_NEWTON = MODE == TEAM_GN;
     constexpr bool ONE_MARCH = POSE && MODE == TEAM_FUSED;  // pose sums of the compositing march
     constexpr bool KEEP = (GRID && MODE == TEAM_FUSED) || GAUSS_NEWTON;   // windows kept for the second pass
-    extern __shared__ float smem[];
+    extern __shared__ __align__(16) float smem[];
     WaveStage wc{};
     if (GRID) wc = wave_stage(smem, io.grad, (uint64_t)g.n_alloc * (RecL<DEG>::S * sizeof(float)));
     const int lane = lane_id();
