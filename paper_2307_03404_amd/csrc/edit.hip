@@ -338,7 +338,10 @@ __device__ __forceinline__ void fine_values(const float v[8][4], int c, float sc
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-constexpr uint32_t NOWHERE = 0xffffffffu;   // no record: beyond every buffer
+// No record: past the end of every buffer, on a 16-byte boundary, and the 16 bytes
+// from it end before the offset wraps to the buffer's start.
+constexpr uint32_t NOWHERE = 0xfffffff0u;
+static_assert(NOWHERE % 16 == 0 && NOWHERE + 12u > NOWHERE, "each word of an access there is out of range");
 
 // Float4s of an array of records, by byte offset.  Not WIDE: a buffer resource of
 // the array's size (under 4 GiB), past whose end a load gives 0 and a store does
