@@ -24,7 +24,7 @@
 // and 1120: a chain of barriers per sub-block and 13 scattered LDS reads per
 // field.  The vector ALU is then busy half of the time, and the L2s fetch the
 // records three times over (halos, and rows that leave L2 before their turn).
-// Cubes of 2^3 blocks dealt to the XCDs in turn: one contiguous eighth each gave
+// Cubes of 2^3 blocks (on flat lattices 8 blocks in another shape) dealt to the XCDs in turn: one contiguous eighth each gave
 // 266 and 665 us (an XCD with a whole wall of the room works longest), single
 // blocks in turn 240 and 527, cubes of 4^3 233 and 538.
 //
@@ -38,9 +38,10 @@ namespace pxm {
 constexpr int TB8 = 8;                  // block edge (vertices)
 constexpr int TH8 = TB8 + 2;            // with halo
 constexpr int TH83 = TH8 * TH8 * TH8;   // 1000 link positions
-constexpr int CUBE = 2;                 // blocks per axis of a cube
+constexpr int PER_CUBE = 8;             // blocks of a cube
 constexpr uint32_t NONE = 0xffffffffu;  // no record
 constexpr int TV_THREADS = 256;
+constexpr int64_t TV_LAUNCH = 1 << 23;  // blocks per launch: a grid holds fewer than 2^32 threads
 // a listed vertex: its position in the halo block and the TV terms that touch
 // it (its own, and those of its -x, -y, -z neighbours)
 constexpr int TERM_POS = 0x3ff, TERM_OWN = 0x400, TERM_X = 0x800, TERM_Y = 0x1000, TERM_Z = 0x2000;
@@ -86,11 +87,17 @@ __device__ __forceinline__ float tv_field(const TvHood& h, int e, float eps) {
     return acc;
 }
 
+// Cubes along y and z, and the logarithm of a cube's blocks along each axis.
+struct TvCubes {
+    int ny, nz, lx, ly, lz;
+};
+
+// first: the launch's first block (a launch holds at most TV_LAUNCH of them).
 // WIDE: the map's records span 4 GiB or more; otherwise s_rec holds byte offsets,
 // and an address is one 32-bit add.
 template <int DEG, bool SET, bool NORMAL, bool WIDE>
 __global__ void __launch_bounds__(TV_THREADS) k_tv(KGrid g, float lam_d, float lam_sh, float eps,
-                                                   float* __restrict__ grad, int ncy, int ncz) {
+                                                   float* __restrict__ grad, TvCubes cs, int64_t first) {
     constexpr int S = RecL<DEG>::S, Q = RecL<DEG>::Q, USED = RecL<DEG>::USED;
     __shared__ uint32_t s_rec[TH83];        // records of the block and its halo (NONE: empty or outside)
     __shared__ int s_list[TB8 * TB8 * TB8]; // its allocated vertices
@@ -99,12 +106,13 @@ __global__ void __launch_bounds__(TV_THREADS) k_tv(KGrid g, float lam_d, float l
     // Cubes of blocks go round the XCDs (workgroup b runs on XCD b mod 8), so
     // that blocks sharing halos share an L2 and no XCD gets a whole wall of the
     // map; the turn shifts from round to round, as a row of cubes may hold eight.
-    constexpr int PER_CUBE = CUBE * CUBE * CUBE;
-    const int64_t round = blockIdx.x / (8 * PER_CUBE);
-    const int64_t cube = round * 8 + ((blockIdx.x + 3 * round + round / 8) & 7);
-    const int in = (int)((blockIdx.x / 8) % PER_CUBE);
-    const int bz = (int)(cube % ncz) * CUBE + in % CUBE, by = (int)((cube / ncz) % ncy) * CUBE + (in / CUBE) % CUBE;
-    const int bx = (int)(cube / ((int64_t)ncz * ncy)) * CUBE + in / (CUBE * CUBE);
+    const int64_t b = first + blockIdx.x;
+    const int64_t round = b / (8 * PER_CUBE);
+    const int64_t cube = round * 8 + ((b + 3 * round + round / 8) & 7);
+    const int in = (int)((b / 8) % PER_CUBE);
+    const int bz = ((int)(cube % cs.nz) << cs.lz) + (in & ((1 << cs.lz) - 1));
+    const int by = ((int)((cube / cs.nz) % cs.ny) << cs.ly) + ((in >> cs.lz) & ((1 << cs.ly) - 1));
+    const int bx = ((int)(cube / ((int64_t)cs.nz * cs.ny)) << cs.lx) + (in >> (cs.lz + cs.ly));
     const int x0 = bx * TB8, y0 = by * TB8, z0 = bz * TB8;
     const int X = g.R[0], Y = g.R[1], Z = g.R[2];
     if (x0 >= X || y0 >= Y || z0 >= Z) return;              // workgroup-uniform, as below
@@ -208,14 +216,25 @@ __global__ void __launch_bounds__(TV_THREADS) k_tv(KGrid g, float lam_d, float l
 template <int DEG, bool SET>
 static void tv_go(const KGrid& g, float lambda_density, float lambda_sh, float eps, float* grad_data,
                   hipStream_t st) {
-    int nc[3];
-    for (int a = 0; a < 3; ++a) nc[a] = (g.R[a] + TB8 * CUBE - 1) / (TB8 * CUBE);
-    const int64_t rounds = ((int64_t)nc[0] * nc[1] * nc[2] + 7) / 8;
-    const dim3 blocks((unsigned)(rounds * 8 * CUBE * CUBE * CUBE)), threads(TV_THREADS);
+    // A cube of 8 blocks is halved along the axes in turn, but not along one that
+    // has no second block to share it with: half of the workgroups would be empty.
+    int nb[3], l[3] = {0, 0, 0}, nc[3];
+    for (int a = 0; a < 3; ++a) nb[a] = (g.R[a] + TB8 - 1) / TB8;
+    for (int k = 0; k < 3; ++k) {
+        int best = -1;
+        for (int a = 2; a >= 0; --a)
+            if ((nb[a] >> l[a]) > 1 && (best < 0 || l[a] < l[best])) best = a;
+        ++l[best < 0 ? 2 : best];
+    }
+    for (int a = 0; a < 3; ++a) nc[a] = (nb[a] + (1 << l[a]) - 1) >> l[a];
+    const TvCubes cs = {nc[1], nc[2], l[0], l[1], l[2]};
+    const int64_t blocks = ((int64_t)nc[0] * nc[1] * nc[2] + 7) / 8 * (8 * PER_CUBE);
     const bool normal = eps >= 1.17549435e-38f;
     const bool wide = (uint64_t)g.n_alloc * (RecL<DEG>::S * sizeof(float)) >= NONE;
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, blocks, threads, 0, st, g, lambda_density, lambda_sh, eps, grad_data, nc[1], nc[2]);
+        for (int64_t first = 0; first < blocks; first += TV_LAUNCH)
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks - first < TV_LAUNCH ? blocks - first : TV_LAUNCH)), dim3(TV_THREADS), 0, st,
+                               g, lambda_density, lambda_sh, eps, grad_data, cs, first);
     };
     if (wide) normal ? go(k_tv<DEG, SET, true, true>) : go(k_tv<DEG, SET, false, true>);
     else normal ? go(k_tv<DEG, SET, true, false>) : go(k_tv<DEG, SET, false, false>);
