@@ -87,6 +87,10 @@ hipError_t team_fused(const KGrid& g, const KRays& rs, const KOpts& op, int log_
 // set: grad_data = dTV for the visited records' used fields, else += dTV
 hipError_t launch_tv(const KGrid& g, float lambda_density, float lambda_sh, float eps,
                      float* grad_data, bool set, hipStream_t st);
+// its form for large maps that allocate most of their lattice (tv_staged.hip), and whether the map is one
+bool tv_staged_wins(const KGrid& g);
+hipError_t launch_tv_staged(const KGrid& g, float lambda_density, float lambda_sh, float eps, float* grad_data, bool set,
+                            hipStream_t st);
 
 // Occupancy bitfield: level-0 32-bit words (two per 4^3-cell block), 4^3
 // blocks per axis, 8^3 bricks per axis, level-1 words for a lattice of R

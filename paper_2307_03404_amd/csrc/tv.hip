@@ -242,6 +242,7 @@ static void tv_go(const KGrid& g, float lambda_density, float lambda_sh, float e
 
 hipError_t launch_tv(const KGrid& g, float lambda_density, float lambda_sh, float eps,
                      float* grad_data, bool set, hipStream_t st) {
+    if (tv_staged_wins(g)) return launch_tv_staged(g, lambda_density, lambda_sh, eps, grad_data, set, st);
     auto by_set = [&](auto D) {
         constexpr int DEG = decltype(D)::value;
         if (set) tv_go<DEG, true>(g, lambda_density, lambda_sh, eps, grad_data, st);
