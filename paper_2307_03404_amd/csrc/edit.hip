@@ -261,28 +261,29 @@ __global__ __launch_bounds__(EDIT_THREADS) void k_grow_flags(const uint32_t* __r
     finish_chunk(bits, gw, nw, words, wpre, chunk_total);
 }
 
-// One wave per fine row, 4 links per lane and ROW_STEPS steps of 256 requested
-// together: the row is the same on the whole wave, so a link costs a shift, a
-// popcount and a quarter of a store.  Bound by the writes: 511^3 links 115 us (537 MB
-// written), 220 where each lane found the row of its link by division.
+// A group of lanes per fine row (the power of two that ROW_STEPS steps of 4 links per
+// lane fill, a whole wave from 257 links on), whose steps are requested together: a
+// link costs a shift, a popcount and a quarter of a store.  Bound by the writes:
+// 511^3 links 115 us (537 MB written), 220 where each lane found the row of its link by
+// division; 2047 x 2047 x 15 links with their count 225 us, 809 with a wave to every row.
 constexpr int ROW_STEPS = 2;
 
-__global__ __launch_bounds__(EDIT_THREADS) void k_fine_link(Lattice L, const uint32_t* __restrict__ words,
+__global__ __launch_bounds__(EDIT_THREADS) void k_fine_link(Lattice L, int log_g, const uint32_t* __restrict__ words,
                                                             const int32_t* __restrict__ wpre,
                                                             const int32_t* __restrict__ chunk_off,
                                                             int32_t* __restrict__ link_fine) {
-    const int lane = lane_id();
+    const int group = 1 << log_g, lane = threadIdx.x & (group - 1);
     const int64_t rows = (int64_t)L.Rf[0] * L.Rf[1];
-    const int64_t waves = (int64_t)gridDim.x * (EDIT_THREADS / WAVE);
-    for (int64_t row = (int64_t)blockIdx.x * (EDIT_THREADS / WAVE) + threadIdx.x / WAVE; row < rows; row += waves) {
+    const int64_t groups = (int64_t)gridDim.x * (EDIT_THREADS >> log_g);
+    for (int64_t row = (int64_t)blockIdx.x * (EDIT_THREADS >> log_g) + (threadIdx.x >> log_g); row < rows; row += groups) {
         const int64_t w0 = row * L.WF;
         int32_t* out = link_fine + row * L.Rf[2];
-        for (int z0 = 0; z0 < L.Rf[2]; z0 += ROW_STEPS * WAVE * 4) {
+        for (int z0 = 0; z0 < L.Rf[2]; z0 += ROW_STEPS * group * 4) {
             uint32_t bits[ROW_STEPS];
             int32_t base[ROW_STEPS];
 #pragma unroll
             for (int k = 0; k < ROW_STEPS; ++k) {
-                const int z = z0 + (k * WAVE + lane) * 4;
+                const int z = z0 + (k * group + lane) * 4;
                 bits[k] = 0u;
                 base[k] = 0;
                 if (z < L.Rf[2]) {
@@ -293,7 +294,7 @@ __global__ __launch_bounds__(EDIT_THREADS) void k_fine_link(Lattice L, const uin
             }
 #pragma unroll
             for (int k = 0; k < ROW_STEPS; ++k) {
-                const int z = z0 + (k * WAVE + lane) * 4, b = z & 31;
+                const int z = z0 + (k * group + lane) * 4, b = z & 31;
                 int32_t id = base[k] + __popc(bits[k] & ((1u << b) - 1u));
                 int32_t l[4];
 #pragma unroll
@@ -378,8 +379,8 @@ struct Records {
 // Records by coarse vertex: coarse vertex v owns the fine vertices
 // 2v + o, o in {0,1}^3, and all eight interpolate from the corners v + o' of
 // coarse cell v (o' a subset of o's bits; weight 1/2 per odd axis).  A wave
-// takes 64 coarse vertices of one row, a lane each: it reads their fine links
-// and lists, in LDS, the records around those with an allocated fine vertex (a
+// takes 64 coarse vertices, a lane each (of one row, or of several rows of at most
+// 32): it reads their fine links and lists, in LDS, the records around those with an allocated fine vertex (a
 // tenth of a sparse map's).  Then a group of 8 lanes takes a listed vertex: lane
 // p < S/4 (7 at SH degree 2) fetches float4 p of the 8 corner records and writes
 // float4 p of each allocated fine record.
@@ -389,19 +390,20 @@ struct Records {
 // Requesting the next vertex's records early, two z-neighbours' records in one
 // store and other orders over the XCDs were no faster.
 template <bool WIDE>
-__global__ __launch_bounds__(EDIT_THREADS) void k_fine_data(KGrid g, Lattice L, const int32_t* __restrict__ link_fine,
+__global__ __launch_bounds__(EDIT_THREADS) void k_fine_data(KGrid g, Lattice L, int log_g, const int32_t* __restrict__ link_fine,
                                                             int64_t n_fine, float* __restrict__ out) {
     __shared__ u32x4 s_keys[EDIT_THREADS / WAVE][WAVE][4];   // per listed vertex: 8 corner records, 8 fine records
     const int lane = lane_id(), wave = threadIdx.x / WAVE;
-    const int segs = (L.R[2] + WAVE - 1) / WAVE;             // 64-vertex segments per row
-    const int64_t items = (int64_t)L.R[0] * L.R[1] * segs;
+    const int group = 1 << log_g, per_wave = WAVE >> log_g;  // lanes per row segment, segments per wave
+    const int segs = (L.R[2] + group - 1) / group;           // segments per row
+    const int64_t rows = (int64_t)L.R[0] * L.R[1], items = (rows * segs + per_wave - 1) / per_wave;
     const int64_t waves = (int64_t)gridDim.x * (EDIT_THREADS / WAVE);
     const int S = record_floats(g.deg), Q = S / 4;           // float4 parts per record (at most 7)
     const Records<WIDE> src(const_cast<float*>(g.data), g.n_alloc, S), dst(out, n_fine, S);
     for (int64_t it = ray_tile(blockIdx.x, gridDim.x) * (EDIT_THREADS / WAVE) + wave; it < items; it += waves) {
-        const int64_t row = it / segs;
-        const int vx = (int)(row / L.R[1]), vy = (int)(row - (int64_t)vx * L.R[1]);
-        const int vz = (int)(it - row * segs) * WAVE + lane;
+        const uint32_t seg = (uint32_t)(it * per_wave) + (lane >> log_g), row = seg / (uint32_t)segs;   // fewer than 2^31
+        const int vx = (int)(row / (uint32_t)L.R[1]), vy = (int)(row - (uint32_t)vx * L.R[1]);   // vx past the lattice: no vertex
+        const int vz = (int)(seg - row * segs) * group + (lane & (group - 1));
         int32_t l[8], f[8];
         bool any = false;
 #pragma unroll
@@ -481,6 +483,13 @@ unsigned stride_blocks(int64_t items, int per_block = EDIT_THREADS) {
     return (unsigned)(b < 1 ? 1 : b > (1 << 20) ? (1 << 20) : b);
 }
 
+// Lanes for a row of n items, per_lane to a lane: the logarithm of a power of two, at most a wave.
+int group_log2(int n, int per_lane) {
+    int lg = 0;
+    while (lg < 6 && per_lane << lg < n) ++lg;
+    return lg;
+}
+
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 Lattice lattice(const KGrid& g) {
@@ -546,7 +555,8 @@ hipError_t launch_upsample_link(const KGrid& g, int32_t* link_fine, int64_t* n_f
                        c.wpre, c.chunk);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = scan(c, n_fine, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_fine_link, dim3(stride_blocks(rows_f, EDIT_THREADS / WAVE)), dim3(EDIT_THREADS), 0, st, L, c.words,
+    const int log_g = group_log2(L.Rf[2], 4 * ROW_STEPS);
+    hipLaunchKernelGGL(k_fine_link, dim3(stride_blocks(rows_f, EDIT_THREADS >> log_g)), dim3(EDIT_THREADS), 0, st, L, log_g, c.words,
                        c.wpre, c.chunk, link_fine);
     return hipGetLastError();
 }
@@ -554,9 +564,12 @@ hipError_t launch_upsample_link(const KGrid& g, int32_t* link_fine, int64_t* n_f
 hipError_t launch_upsample_data(const KGrid& g, const int32_t* link_fine, int64_t n_fine, float* data_fine,
                                 hipStream_t st) {
     const Lattice L = lattice(g);
-    const int64_t items = (int64_t)L.R[0] * L.R[1] * ((L.R[2] + WAVE - 1) / WAVE);   // a wave each
+    // a row of at most 32 vertices shares its wave: 1024 x 1024 x 8 vertices, one in
+    // a hundred allocated, 393 us, 996 with a wave to every row
+    const int log_g = group_log2(L.R[2], 1);
+    const int64_t segs = (int64_t)L.R[0] * L.R[1] * ((L.R[2] + (1 << log_g) - 1) >> log_g);
     const uint64_t bytes = (uint64_t)(g.n_alloc > n_fine ? g.n_alloc : n_fine) * (4 * record_floats(g.deg));
-    hipLaunchKernelGGL(bytes < NOWHERE ? k_fine_data<false> : k_fine_data<true>, dim3(stride_blocks(items, EDIT_THREADS / WAVE)), dim3(EDIT_THREADS), 0, st, g, L, link_fine,
+    hipLaunchKernelGGL(bytes < NOWHERE ? k_fine_data<false> : k_fine_data<true>, dim3(stride_blocks(segs, EDIT_THREADS >> log_g)), dim3(EDIT_THREADS), 0, st, g, L, log_g, link_fine,
                        n_fine, data_fine);
     return hipGetLastError();
 }
