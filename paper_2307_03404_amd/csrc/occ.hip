@@ -24,22 +24,26 @@ void occ_layout(const int R[3], int64_t& w0_words, int Q[3], int B[3], int64_t& 
     w1_words = ((int64_t)B[0] * B[1] * B[2] + 31) / 32;
 }
 
-// A wave per 4 x 4 cells of (x, y) and OCC_RUN blocks along z: the 5 x 5 rows of 64
-// links it needs are requested at once, each row's ballot is its allocation bits,
-// a cell's bit along z is its own or the next, rows of cells are ORs of four
-// rows of vertices, and lane l assembles the word of block l.  Bound by the
-// link reads (511^3: 152 us; a lane per cell that read its own 8 corners took 506,
-// reading the table once takes 105).
+// A group of lanes per 4 x 4 cells of (x, y) and a run of blocks along z: the 5 x 5
+// rows of links it needs, one link per lane, are requested at once, each row's
+// ballot is its allocation bits, a cell's bit along z is its own or the next, rows of
+// cells are ORs of four rows of vertices, and lane l assembles the word of block l.
+// A group is a wave (runs of OCC_RUN blocks), or the 4 to 32 lanes that hold a short
+// row whole.  Bound by the link reads (511^3: 152 us; a lane per cell that read its
+// own 8 corners took 506, reading the table once takes 105; 1024 x 1024 x 8 14 us, 61
+// with a wave to every row).
 constexpr int OCC_RUN = 15;                                 // 60 cells, 61 of the 64 vertices
 
-__global__ void __launch_bounds__(256) k_occ0(KGrid g, uint64_t* __restrict__ occ0, int64_t n_items, int runs) {
-    const int lane = lane_id();
+__global__ void __launch_bounds__(256) k_occ0(KGrid g, uint64_t* __restrict__ occ0, int64_t n_items, int runs, int log_g) {
+    const int group = 1 << log_g, in = lane_id() & (group - 1), first = lane_id() - in;
     const int64_t waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
-    for (int64_t it = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE; it < n_items; it += waves) {
+    const int64_t n_waves = (n_items + (WAVE >> log_g) - 1) >> (6 - log_g);
+    for (int64_t w = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE; w < n_waves; w += waves) {
+        const int64_t it = (w << (6 - log_g)) + (first >> log_g);
         const int64_t q2 = it / runs;
         const int qz = (int)(it - q2 * runs) * OCC_RUN;
         const int qx = (int)(q2 / g.Q[1]), qy = (int)(q2 - (int64_t)qx * g.Q[1]);
-        const int x0 = 4 * qx, y0 = 4 * qy, z = 4 * qz + lane;
+        const int x0 = 4 * qx, y0 = 4 * qy, z = 4 * qz + in;   // x0 past the lattice: no cells
         int32_t l[25];
 #pragma unroll
         for (int k = 0; k < 25; ++k) {
@@ -50,18 +54,19 @@ __global__ void __launch_bounds__(256) k_occ0(KGrid g, uint64_t* __restrict__ oc
         unsigned long long row[25];
 #pragma unroll
         for (int k = 0; k < 25; ++k) row[k] = __ballot((uint32_t)l[k] < (uint64_t)g.n_alloc);
-        // cells beyond R - 2 on an axis are empty
+        // cells beyond R - 2 on an axis are empty, and so is what another group's bits
+        // shift in: a group holds a vertex more than its cells
         const int cells = g.R[2] - 1 - 4 * qz;
-        const unsigned long long in_z = cells >= 64 ? ~0ull : (1ull << cells) - 1ull;
+        const unsigned long long in_z = (cells >= 64 ? ~0ull : (1ull << cells) - 1ull) << first;
         uint64_t word = 0ull;
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
             const int cx = c >> 2, cy = c & 3, k = 5 * cx + cy;
             unsigned long long m = row[k] | row[k + 1] | row[k + 5] | row[k + 6];
             m = x0 + cx < g.R[0] - 1 && y0 + cy < g.R[1] - 1 ? (m | (m >> 1)) & in_z : 0ull;
-            word |= ((m >> (4 * (lane & 15))) & 0xfull) << (4 * c);
+            word |= ((m >> ((first + 4 * in) & 63)) & 0xfull) << (4 * c);
         }
-        if (lane < OCC_RUN && qz + lane < g.Q[2]) occ0[q2 * g.Q[2] + qz + lane] = word;
+        if (in < OCC_RUN && 4 * in < group && qz + in < g.Q[2] && it < n_items) occ0[q2 * g.Q[2] + qz + in] = word;
     }
 }
 
@@ -99,9 +104,11 @@ hipError_t launch_occupancy(const KGrid& g, uint32_t* occ, hipStream_t st) {
     }
     const int runs = (Q[2] + OCC_RUN - 1) / OCC_RUN;
     const int64_t n_items = (int64_t)Q[0] * Q[1] * runs;
-    const int64_t wgs = (n_items + 3) / 4;                // four waves per workgroup
+    int log_g = 2;                                        // lanes that hold a whole row of vertices, or a wave
+    while (log_g < 6 && (1 << log_g) < g.R[2]) ++log_g;
+    const int64_t per_wg = (int64_t)(256 >> log_g), wgs = (n_items + per_wg - 1) / per_wg;
     hipLaunchKernelGGL(k_occ0, dim3((unsigned)(wgs < (1 << 20) ? wgs : (1 << 20))), dim3(256), 0, st, k,
-                       reinterpret_cast<uint64_t*>(occ), n_items, runs);
+                       reinterpret_cast<uint64_t*>(occ), n_items, runs, log_g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t nb = (int64_t)B[0] * B[1] * B[2];

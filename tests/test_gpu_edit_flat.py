@@ -1,4 +1,4 @@
-"""Grid growth on lattices with short rows along z, whose
+"""Grid growth and the occupancy bitfield on lattices with short rows along z, whose
 rows share a wave (2 to 64 vertices, and the lengths on either side of each number
 of lanes a row gets), bit for bit against the oracle."""
 import numpy as np
@@ -6,6 +6,7 @@ import pytest
 
 import oracle
 from paper_2307_03404_amd import synth
+from tests.test_gpu_parity import _occupancy_numpy
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -24,6 +25,7 @@ def test_short_rows(R, share):
     grid = synth.grid_from_mask(R, (0.0, 0.0, 0.0), 0.1, mask, rng.normal(size=int(mask.sum())).astype(np.float32), rng)
     print(f"[gpu] edit {R} share {share}: {grid.n_alloc} records", flush=True)
     g = pxm.grid_to_device(grid)
+    np.testing.assert_array_equal(g.occ.cpu().numpy().view(np.uint32), _occupancy_numpy(grid))
     want = oracle.grid_upsample(grid)
     got = pxm.grid_upsample(g)
     np.testing.assert_array_equal(got.link.cpu().numpy(), want.link)
