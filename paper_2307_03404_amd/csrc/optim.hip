@@ -65,66 +65,116 @@ hipError_t launch_rmsprop(int64_t n, int deg, float* data, float* grad, float* a
     return hipGetLastError();
 }
 
-// Ray batch of a mapping iteration, in one launch: workgroup 0 counts the valid
-// target depths and finds the frames' offsets (the indices ascend, so frame f
-// starts at the first index that is not below its keyframe offset); the others
-// copy a ray per lane.  13 launches of elementwise and index kernels and a
-// host synchronisation before.
+// Ray batch of a mapping iteration.  Up to GATHER_ONE rays in one launch: workgroup 0
+// counts the valid target depths and finds the frames' offsets (the indices ascend, so
+// frame f starts at the first index that is not below its keyframe offset); the others
+// copy a ray per lane.  13 launches of elementwise and index kernels and a host
+// synchronisation before.  That count is one workgroup's chain of dependent loads and
+// grows with the batch; larger batches count where they copy, with one atomic per
+// workgroup into frame_offsets[0], which a launch before clears and one after reads.
+// us of one launch and of three, rays of 6.5 M: 2,048 6.8 and 12.5; 8,192 8.3 and 12.9;
+// 16,384 21.9 and 13.2; 65,536 86.7 and 16.2; 1,048,576 642 and 43.
 constexpr int COUNT_THREADS = 1024;
+constexpr int64_t GATHER_ONE = 8192;
 
-__global__ void __launch_bounds__(COUNT_THREADS) k_gather_rays(int64_t n, const int64_t* __restrict__ index, int64_t n_kf, int F,
-                                                               const int32_t* __restrict__ kf_off,
-                                                               const int32_t* __restrict__ kf_pix,
-                                                               const float* __restrict__ kf_rgb,
-                                                               const float* __restrict__ kf_depth,
-                                                               int32_t* __restrict__ pix, float* __restrict__ rgb,
-                                                               float* __restrict__ depth, int32_t* __restrict__ off,
-                                                               float* __restrict__ weight) {
-    auto ray = [&](int64_t r) -> int64_t {
-        const int64_t i = index[r];
-        return i < 0 ? 0 : i >= n_kf ? n_kf - 1 : i;
-    };
-    if (blockIdx.x > 0) {
-        const int64_t r = (int64_t)(blockIdx.x - 1) * COUNT_THREADS + threadIdx.x;
-        if (r >= n) return;
-        const int64_t i = ray(r);
-        pix[2 * r] = kf_pix[2 * i];
-        pix[2 * r + 1] = kf_pix[2 * i + 1];
-        rgb[3 * r] = kf_rgb[3 * i];
-        rgb[3 * r + 1] = kf_rgb[3 * i + 1];
-        rgb[3 * r + 2] = kf_rgb[3 * i + 2];
-        depth[r] = kf_depth[i];
-        return;
-    }
+struct GatherIO {
+    const int64_t* index;
+    int64_t n, n_kf;
+    int F;
+    const int32_t* kf_off;
+    const int32_t* kf_pix;
+    const float* kf_rgb;
+    const float* kf_depth;
+    int32_t* pix;
+    float* rgb;
+    float* depth;
+    int32_t* off;
+    float* weight;
+};
+
+// Keyframe ray of ray r of the batch, inside the keyframes whatever the index says.
+__device__ __forceinline__ int64_t gather_index(const GatherIO& io, int64_t r) {
+    const int64_t i = io.index[r];
+    return i < 0 ? 0 : i >= io.n_kf ? io.n_kf - 1 : i;
+}
+
+__device__ __forceinline__ bool gather_ray(const GatherIO& io, int64_t r) {
+    const int64_t i = gather_index(io, r);
+    io.pix[2 * r] = io.kf_pix[2 * i];
+    io.pix[2 * r + 1] = io.kf_pix[2 * i + 1];
+    io.rgb[3 * r] = io.kf_rgb[3 * i];
+    io.rgb[3 * r + 1] = io.kf_rgb[3 * i + 1];
+    io.rgb[3 * r + 2] = io.kf_rgb[3 * i + 2];
+    const float d = io.kf_depth[i];
+    io.depth[r] = d;
+    return isfinite(d) && d > 0.f;
+}
+
+// Sum over the workgroup, returned to all of its threads.
+__device__ __forceinline__ long long block_count(long long count) {
     __shared__ long long s_count[COUNT_THREADS / WAVE];
-    long long count = 0;
-    for (int64_t r = threadIdx.x; r < n; r += COUNT_THREADS) {
-        const float d = kf_depth[ray(r)];
-        count += isfinite(d) && d > 0.f;
-    }
     count = wave_sum(count);
     if (lane_id() == 0) s_count[threadIdx.x / WAVE] = count;
     __syncthreads();
     count = 0;
     for (int w = 0; w < COUNT_THREADS / WAVE; ++w) count += s_count[w];
+    return count;
+}
+
+// One workgroup: the frames' offsets and weights of a batch with `count` valid depths.
+__device__ __forceinline__ void gather_frames(const GatherIO& io, long long count) {
     const float m = 1.0f / (float)(count < 1 ? 1 : count);
-    for (int f = threadIdx.x; f <= F; f += COUNT_THREADS) {
-        int64_t lo = 0, hi = n;                             // first r with ray(r) >= kf_off[f]
+    for (int f = threadIdx.x; f <= io.F; f += COUNT_THREADS) {
+        int64_t lo = 0, hi = io.n;                          // first r with an index >= kf_off[f]
         while (lo < hi) {
             const int64_t mid = (lo + hi) / 2;
-            if (ray(mid) < kf_off[f]) lo = mid + 1; else hi = mid;
+            if (gather_index(io, mid) < io.kf_off[f]) lo = mid + 1; else hi = mid;
         }
-        off[f] = (int32_t)(f == 0 ? 0 : f == F ? n : lo);
-        if (f < F) weight[f] = m;
+        io.off[f] = (int32_t)(f == 0 ? 0 : f == io.F ? io.n : lo);
+        if (f < io.F) io.weight[f] = m;
     }
+}
+
+__global__ void __launch_bounds__(COUNT_THREADS) k_gather_rays(GatherIO io) {
+    if (blockIdx.x > 0) {
+        const int64_t r = (int64_t)(blockIdx.x - 1) * COUNT_THREADS + threadIdx.x;
+        if (r < io.n) gather_ray(io, r);
+        return;
+    }
+    long long count = 0;
+    for (int64_t r = threadIdx.x; r < io.n; r += COUNT_THREADS) {
+        const float d = io.kf_depth[gather_index(io, r)];
+        count += isfinite(d) && d > 0.f;
+    }
+    gather_frames(io, block_count(count));
+}
+
+__global__ void k_gather_clear(int32_t* count) { *count = 0; }
+
+__global__ void __launch_bounds__(COUNT_THREADS) k_gather_copy(GatherIO io) {
+    const int64_t r = (int64_t)blockIdx.x * COUNT_THREADS + threadIdx.x;
+    const long long count = block_count(r < io.n && gather_ray(io, r));
+    if (threadIdx.x == 0 && count > 0) atomicAdd(io.off, (int32_t)count);
+}
+
+__global__ void __launch_bounds__(COUNT_THREADS) k_gather_frames(GatherIO io) {
+    const int32_t count = *io.off;
+    __syncthreads();                                        // all have read it: it becomes the first offset
+    gather_frames(io, count);
 }
 
 hipError_t launch_gather_rays(int64_t n, const int64_t* index, int64_t n_kf, int F, const int32_t* kf_off, const int32_t* kf_pix,
                               const float* kf_rgb, const float* kf_depth, int32_t* pix, float* rgb, float* depth,
                               int32_t* off, float* weight, hipStream_t st) {
-    const unsigned blocks = 1 + (unsigned)((n + COUNT_THREADS - 1) / COUNT_THREADS);
-    hipLaunchKernelGGL(k_gather_rays, dim3(blocks), dim3(COUNT_THREADS), 0, st, n, index, n_kf, F, kf_off, kf_pix, kf_rgb,
-                       kf_depth, pix, rgb, depth, off, weight);
+    const GatherIO io = {index, n, n_kf, F, kf_off, kf_pix, kf_rgb, kf_depth, pix, rgb, depth, off, weight};
+    const unsigned blocks = (unsigned)((n + COUNT_THREADS - 1) / COUNT_THREADS);
+    if (n <= GATHER_ONE) {
+        hipLaunchKernelGGL(k_gather_rays, dim3(1 + blocks), dim3(COUNT_THREADS), 0, st, io);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_gather_clear, dim3(1), dim3(1), 0, st, off);
+    hipLaunchKernelGGL(k_gather_copy, dim3(blocks), dim3(COUNT_THREADS), 0, st, io);
+    hipLaunchKernelGGL(k_gather_frames, dim3(1), dim3(COUNT_THREADS), 0, st, io);
     return hipGetLastError();
 }
 
