@@ -73,7 +73,7 @@ hipError_t launch_rmsprop(int64_t n, int deg, float* data, float* grad, float* a
 // grows with the batch; larger batches count where they copy, with one atomic per
 // workgroup into frame_offsets[0], which a launch before clears and one after reads.
 // us of one launch and of three, rays of 6.5 M: 2,048 6.8 and 12.5; 8,192 8.3 and 12.9;
-// 16,384 21.9 and 13.2; 65,536 86.7 and 16.2; 1,048,576 642 and 43.
+// 16,384 22 and 13; 65,536 87 and 14; 1,048,576 642 and 35.
 constexpr int COUNT_THREADS = 1024;
 constexpr int64_t GATHER_ONE = 8192;
 
@@ -100,12 +100,14 @@ __device__ __forceinline__ int64_t gather_index(const GatherIO& io, int64_t r) {
 
 __device__ __forceinline__ bool gather_ray(const GatherIO& io, int64_t r) {
     const int64_t i = gather_index(io, r);
-    io.pix[2 * r] = io.kf_pix[2 * i];
-    io.pix[2 * r + 1] = io.kf_pix[2 * i + 1];
-    io.rgb[3 * r] = io.kf_rgb[3 * i];
-    io.rgb[3 * r + 1] = io.kf_rgb[3 * i + 1];
-    io.rgb[3 * r + 2] = io.kf_rgb[3 * i + 2];
-    const float d = io.kf_depth[i];
+    // all loads before the first store: the arrays are not known to be apart
+    const int32_t u = io.kf_pix[2 * i], v = io.kf_pix[2 * i + 1];
+    const float c0 = io.kf_rgb[3 * i], c1 = io.kf_rgb[3 * i + 1], c2 = io.kf_rgb[3 * i + 2], d = io.kf_depth[i];
+    io.pix[2 * r] = u;
+    io.pix[2 * r + 1] = v;
+    io.rgb[3 * r] = c0;
+    io.rgb[3 * r + 1] = c1;
+    io.rgb[3 * r + 2] = c2;
     io.depth[r] = d;
     return isfinite(d) && d > 0.f;
 }
