@@ -284,12 +284,14 @@ class MappingLoop:
         return idx, rays, rgb, depth, w
 
     def _plain(self):
-        """Keyframe rays and targets as pxm.gather_rays reads them."""
-        kf = self.kf
+        """Keyframe rays and targets as pxm.gather_rays reads them, on the map's GPU and
+        none that autograd follows (its copies would not)."""
+        kf, dev = self.kf, self.grid.data.device
         n, F = int(kf.pix.shape[0]), int(kf.c2w.shape[0])
-        return all(t.is_cuda and t.is_contiguous() and t.dtype == dt and tuple(t.shape) == shape for t, dt, shape in (
-            (kf.pix, torch.int32, (n, 2)), (kf.frame_offsets, torch.int32, (F + 1,)),
-            (self.tgt_rgb, torch.float32, (n, 3)), (self.tgt_depth, torch.float32, (n,))))
+        return all(t.is_cuda and t.device == dev and not t.requires_grad and t.is_contiguous() and t.dtype == dt
+                   and tuple(t.shape) == shape for t, dt, shape in (
+                       (kf.pix, torch.int32, (n, 2)), (kf.frame_offsets, torch.int32, (F + 1,)),
+                       (self.tgt_rgb, torch.float32, (n, 3)), (self.tgt_depth, torch.float32, (n,))))
 
     def grow(self):
         """Coarse-to-fine growth of the map (Sec. 6.1's dynamic grid; see

@@ -67,3 +67,20 @@ def test_replayed_in_a_graph():
         graph.replay()
         torch.cuda.synchronize()
         _same((idx, *out), loop.sample(idx))
+
+
+@pytest.mark.parametrize("which", ["tgt_rgb", "tgt_depth"])
+def test_targets_under_autograd_keep_their_graph(which):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    loop = _loop(100, (300, 40))
+    getattr(loop, which).requires_grad_(True)
+    print(f"[gpu] a batch of {which} that requires a gradient", flush=True)
+    idx, _, rgb, depth, _ = loop.sample()
+    out = rgb if which == "tgt_rgb" else depth
+    assert out.requires_grad
+    out[torch.isfinite(out)].sum().backward()
+    counts = torch.bincount(idx, minlength=340).float()
+    got = getattr(loop, which).grad.reshape(340, -1)[:, 0]
+    ok = torch.isfinite(getattr(loop, which).detach()).reshape(340, -1)[:, 0]
+    assert torch.equal(got[ok], counts[ok])
