@@ -16,7 +16,8 @@
 from __future__ import annotations
 
 import dataclasses
-
+import functools
+import hashlib
 import json
 import os
 import time
@@ -77,13 +78,24 @@ def pack_frames(frames, width: int, tile: int = 8, height: int | None = None) ->
 # autotuner
 # ----------------------------------------------------------------------------
 
-CANDIDATES = [(b, v) for b in (64, 128, 256) for v in (0, 1, 2)]
+# variant 0 has one launch shape, whatever the block
+CANDIDATES = [(256, 0)] + [(b, v) for b in (64, 128, 256) for v in (1, 2)]
+
+
+@functools.lru_cache(maxsize=4)
+def _library_digest(path: str, mtime_ns: int) -> str:
+    with open(path, "rb") as fh:
+        return hashlib.sha256(fh.read()).hexdigest()[:16]
 
 
 def _signature(grid, rays, opts, want) -> str:
-    return "r%s_n%d_rays%d_f%d_w%d_fl%d_act%d" % (
+    """A problem, and the library whose launch forms were timed on it: what was
+    fastest in another build says nothing about this one."""
+    pxm.lib()
+    lib = _library_digest(pxm.LIB_PATH, os.stat(pxm.LIB_PATH).st_mtime_ns)
+    return "r%s_n%d_rays%d_f%d_w%d_fl%d_act%d_lib%s" % (
         "x".join(str(int(x)) for x in grid.reso), grid.n_alloc, rays.n_rays, rays.n_frames,
-        int(want), int(opts.flags), int(opts.color_act))
+        int(want), int(opts.flags), int(opts.color_act), lib)
 
 
 class Autotuner:
