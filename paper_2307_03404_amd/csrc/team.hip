@@ -22,7 +22,7 @@
 // composited, and Chat_k S is taken off at the end.  The records of a sample
 // are gathered once instead of twice.
 //
-// Gauss-Newton composites first, keeping the positions of its lit windows, then
+// Gauss-Newton composites first, each team keeping the positions of its lit windows, then
 // gathers those again with their spatial derivatives and sums its Jacobian rows
 // in FP32 in sample order, lane after lane: the solve of a badly conditioned
 // frame multiplies their rounding, and its path is then the same at every team
@@ -403,7 +403,7 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
     }
     Carry cy = {0.0, {0.0, 0.0, 0.0}, 0.0, 1.f};
     int64_t kept = 0;                                       // kept sample positions of the ray
-    int windows = 0;                                        // kept windows (the same on the whole wave)
+    int windows = 0;                                        // kept windows: of the wave (grid), of the team (Gauss-Newton)
     bool spilled = false;
     int64_t resume = 0;                                     // the team's position at the first one not kept
     // The march.  A second one goes over the kept positions again: of a ray whose
@@ -448,7 +448,11 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
                 Lit q;
                 composite<ONE_MARCH || SECOND || BACKWARD, !BACKWARD && !SECOND>(op, tm, have, v.sig, v.s, s.t, cy, q,
                                                                                  last);
-                if (KEEP && !SECOND && __ballot(q.lit)) {
+                // the grid gradient keeps the windows of the wave, whose scatters merge; Gauss-Newton
+                // each team its own: the rays of a sparse subset are lit at different samples, and
+                // the wave's windows are then many more (256^3 room, 12 frames of 25k rays, two lanes
+                // per ray: 1018 us, one lane and the wave's windows 1518)
+                if (KEEP && !SECOND && (GRID ? __ballot(q.lit) : __ballot(q.lit) & tm.mask)) {
                     if (windows < KEPT) {
                         if (GRID) keep[windows * WAVE] = make_float4(v.sig, v.s[0], v.s[1], v.s[2]);
                         keep_at[windows * WAVE] = q.lit ? (int32_t)oo : -1;
@@ -582,8 +586,8 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
     }
     if (KEEP) {
         cy = Carry{0.0, {0.0, 0.0, 0.0}, 0.0, 1.f};
-        for (int b = 0; b < windows; ++b) {
-            const int32_t at = keep_at[b * WAVE];
+        for (int b = 0; __ballot(b < windows); ++b) {
+            const int32_t at = b < windows ? keep_at[b * WAVE] : -1;
             const bool have = valid && at >= 0;
             Sample s;
             s.t = 0.f;
@@ -618,7 +622,7 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
                 scatter_merged<DEG>(q.lit, s.base, idx, w, gsig, gs, Y, wc, io.grad);
             }
         }
-        if (spilled) march(std::integral_constant<bool, true>{}, resume, valid ? kept : 0);
+        if (__ballot(spilled)) march(std::integral_constant<bool, true>{}, resume, valid && spilled ? kept : 0);
     }
     if (POSE && !GAUSS_NEWTON) {
         if (ONE_MARCH) {
@@ -783,13 +787,16 @@ hipError_t team_fused(const KGrid& g, const KRays& rs, const KOpts& op, int log_
 
 hipError_t launch_gn(const KGrid& g, const KRays& rs, const KOpts& op, const float* tgt_rgb, const float* tgt_depth,
                      const float* fw, double* gn, hipStream_t st) {
-    // The ordered sums are made for teams of 16, 4, 2 and 1; each stands while its
-    // waves are at most about five per SIMD.  256^3 room, us for T = 1, 2, 4, 16
-    // ("-": one lane per ray, both marches gathering through the work masks):
-    //     2,000 rays  -262 | 341 201 141  57     32,000 rays  -254 | 336 175 125 163
-    //    19,200 rays  -274 | 362 214 152 124    163,200 rays  -506 | 415 386 497
-    //   816,000 rays -2070 | 992 1233
-    const int log_t = rs.n <= 21200 ? 4 : rs.n <= 84800 ? 2 : rs.n <= 169600 ? 1 : 0;
+    // The ordered sums are made for teams of 16, 4, 2 and 1.  Sixteen and four stand while
+    // their waves are at most about five per SIMD, two for longer: rays of a sparse
+    // subset gain from a shorter chain, those of whole frames little.  256^3 room, us for
+    // T = 1, 2, 4, 16 ("-": the kernel before, one lane per ray, both marches through work masks):
+    //   whole frames                             sparse frames
+    //    172,800 rays      472  387  427          64,000 rays -  801 |  828  488  336  398
+    //    307,200 rays      590  570  680         160,000 rays -  830 |  843  554  611  851
+    //    600,000 rays      790  854 1151         300,000 rays - 1124 | 1201 1018 1027 1626
+    //    816,000 rays -2081 | 975 1114 1509      600,000 rays - 1572 | 1691 1495 1822 3105
+    const int log_t = rs.n <= 21200 ? 4 : rs.n <= 84800 ? 2 : rs.n <= 620000 ? 1 : 0;
     TeamIO io{};
     io.tgt_rgb = tgt_rgb;
     io.tgt_depth = tgt_depth;
