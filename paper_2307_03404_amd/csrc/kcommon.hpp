@@ -223,6 +223,48 @@ __device__ __forceinline__ void seg_sum_atomic(int key, bool active, const doubl
     }
 }
 
+constexpr int SUM_WAVES = 4;      // waves of a workgroup that frame_sum takes, at most
+
+// Sums over the rays of each frame, added into out[frame * N + n]: one value
+// set per lane with `active`, keyed by frame.  The waves of a workgroup that
+// hold one frame each (rays are grouped by frame) meet in LDS, so a frame
+// receives one atomic per value and workgroup: atomics on one address are
+// served one after another, 70 ns each, and a wave of 64 lanes per ray holds
+// a single ray.  A workgroup of one wave gains as well: the values leave in one
+// instruction, where seg_sum_atomic sends one each (pose alone, one lane per ray, a
+// frame of 816,000 rays 1247 -> 859 us).  Must be reached by every thread of the workgroup.
+template <int N>
+__device__ __forceinline__ void frame_sum(int key, bool active, const double* vals, double* out) {
+    __shared__ double s_val[SUM_WAVES][N];
+    __shared__ int s_key[SUM_WAVES];
+    const int w = threadIdx.x / WAVE, waves = blockDim.x / WAVE;
+    const unsigned long long any = __ballot(active);
+    const int k0 = any ? __builtin_amdgcn_readlane(key, __ffsll((long long)any) - 1) : -1;
+    const bool one = __ballot(active && key != k0) == 0;
+    if (any == 0) {
+        // a wave without a ray that counts has nothing to sum
+    } else if (one) {
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            const double s = wave_sum(active ? vals[n] : 0.0);
+            if (lane_id() == 0) s_val[w][n] = s;
+        }
+    } else {
+        seg_sum_atomic<N>(key, active, vals, out);
+    }
+    if (lane_id() == 0) s_key[w] = one ? k0 : -1;
+    __syncthreads();
+    if (threadIdx.x < N) {
+        for (int i = 0; i < waves; ++i) {
+            const int k = s_key[i];
+            if (k < 0) continue;
+            double s = s_val[i][threadIdx.x];
+            while (i + 1 < waves && s_key[i + 1] == k) s += s_val[++i][threadIdx.x];
+            atomicAdd(out + (int64_t)k * N + threadIdx.x, s);
+        }
+    }
+}
+
 __device__ __forceinline__ void add_stats(bool active, const long long* v, int64_t* out) {
 #pragma unroll
     for (int n = 0; n < 4; ++n) {

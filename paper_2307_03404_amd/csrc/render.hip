@@ -429,6 +429,49 @@ __global__ void __launch_bounds__(FORWARD_RAYS) k_forward(KGrid g, KRays rs, KOp
     nsamp[r] = fr.n;
 }
 
+// What the backward passes know of a ray: its upstream gradients, and the forward's outputs.
+struct BackwardRay {
+    Ray ray;
+    float Y[9], gC[3], gDr;
+    double Chat[3], Dhat;
+    int f, n;           // frame, positions to replay
+    bool active;        // has an upstream gradient
+};
+
+__device__ __forceinline__ void backward_ray(const KGrid& g, const KRays& rs, const KOpts& op, int64_t r,
+                                             const float* __restrict__ rgb, const float* __restrict__ depth,
+                                             const int32_t* __restrict__ nsamp, const float* __restrict__ g_rgb,
+                                             const float* __restrict__ g_depth, BackwardRay& b) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) b.Y[k] = 0.f;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        b.gC[c] = 0.f;
+        b.Chat[c] = 0.0;
+    }
+    b.gDr = 0.f;
+    b.Dhat = 0.0;
+    b.f = b.n = 0;
+    b.ray.empty = true;
+    b.active = r < rs.n;
+    if (!b.active) return;
+    b.gC[0] = g_rgb[3 * r];
+    b.gC[1] = g_rgb[3 * r + 1];
+    b.gC[2] = g_rgb[3 * r + 2];
+    const float gD = g_depth[r];
+    b.active = b.gC[0] != 0.f || b.gC[1] != 0.f || b.gC[2] != 0.f || gD != 0.f;
+    if (!b.active) return;
+    b.f = frame_of(rs.off, rs.F, r);
+    setup_ray(g, rs, op, r, b.f, b.ray);
+    sh9(b.ray.d[0], b.ray.d[1], b.ray.d[2], b.Y);
+    b.Chat[0] = rgb[3 * r];
+    b.Chat[1] = rgb[3 * r + 1];
+    b.Chat[2] = rgb[3 * r + 2];
+    b.Dhat = (double)depth[r] * (double)b.ray.s;
+    b.gDr = gD / b.ray.s;
+    b.n = b.ray.empty ? 0 : nsamp[r];
+}
+
 // It keeps no work masks, so its LDS (the staging alone) holds 13 waves on a CU,
 // and its 168 registers 3 on a SIMD.  With the mask region allocated, and so 2,
 // the backward of a 1200 x 680 frame of the 256^3 room took 827 us and takes 762,
@@ -444,35 +487,36 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(3, 3)
                                                   float* __restrict__ grad) {
     extern __shared__ __align__(16) float smem[];
     const WaveStage wc = wave_stage(smem, grad, (uint64_t)g.n_alloc * (RecL<DEG>::S * sizeof(float)));
-    const int64_t r = ray_tile(blockIdx.x, gridDim.x) * WAVE + threadIdx.x;
-    bool active = r < rs.n;
-    Ray ray;
+    BackwardRay b;
+    backward_ray(g, rs, op, ray_tile(blockIdx.x, gridDim.x) * WAVE + threadIdx.x, rgb, depth, nsamp, g_rgb, g_depth, b);
     PoseAcc pa = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
-    float Y[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float gC[3] = {0.f, 0.f, 0.f};
-    double Chat[3] = {0.0, 0.0, 0.0};
-    float gDr = 0.f;
-    double Dhat = 0.0;
-    int n = 0;
-    ray.empty = true;
-    if (active) {
-        gC[0] = g_rgb[3 * r];
-        gC[1] = g_rgb[3 * r + 1];
-        gC[2] = g_rgb[3 * r + 2];
-        const float gD = g_depth[r];
-        active = gC[0] != 0.f || gC[1] != 0.f || gC[2] != 0.f || gD != 0.f;
-        if (active) {
-            setup_ray(g, rs, op, r, frame_of(rs.off, rs.F, r), ray);
-            sh9(ray.d[0], ray.d[1], ray.d[2], Y);
-            Chat[0] = rgb[3 * r];
-            Chat[1] = rgb[3 * r + 1];
-            Chat[2] = rgb[3 * r + 2];
-            Dhat = (double)depth[r] * (double)ray.s;
-            gDr = gD / ray.s;
-            n = ray.empty ? 0 : nsamp[r];
-        }
-    }
-    ray_backward<true, false, false, DEG>(g, op, ray, Y, n, Chat, Dhat, gC, gDr, grad, wc, pa);
+    ray_backward<true, false, false, DEG>(g, op, b.ray, b.Y, b.n, b.Chat, b.Dhat, b.gC, b.gDr, grad, wc, pa);
+}
+
+// The pose gradient of batches above POSE_BACKWARD_ONE rays: one lane per ray, one
+// wave per workgroup.  Bound by the latency of its gathers at 2 to 3 waves per SIMD.
+// us of this kernel and of the better of two and four lanes per ray: 160,000 sparse
+// rays of the 256^3 room 602 and 380, 300,000 713 and 660, 600,000 894 and 961 (with
+// the view term 1166 and 1270); frames of 307,200 rays 314 and 365, of 816,000 469 and
+// 629 (564 with one lane in a team); 300,000 rays of the 32^3 map 253 and 320, of a
+// fog in it 783 and 858.
+constexpr int64_t POSE_BACKWARD_ONE = 220000;
+
+template <bool VIEW, int DEG>
+__global__ void __launch_bounds__(WAVE) k_backward_pose(KGrid g, KRays rs, KOpts op, const float* __restrict__ rgb,
+                                                        const float* __restrict__ depth,
+                                                        const int32_t* __restrict__ nsamp,
+                                                        const float* __restrict__ g_rgb,
+                                                        const float* __restrict__ g_depth,
+                                                        double* __restrict__ grad_pose) {
+    BackwardRay b;
+    backward_ray(g, rs, op, ray_tile(blockIdx.x, gridDim.x) * WAVE + threadIdx.x, rgb, depth, nsamp, g_rgb, g_depth, b);
+    PoseAcc pa = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
+    const WaveStage none{};
+    ray_backward<false, true, VIEW, DEG>(g, op, b.ray, b.Y, b.n, b.Chat, b.Dhat, b.gC, b.gDr, nullptr, none, pa);
+    double six[6] = {0, 0, 0, 0, 0, 0};
+    if (b.active) pose_six<VIEW>(b.ray, pa, six);
+    frame_sum<6>(b.f, b.active, six, grad_pose);
 }
 
 // Fused step, in one launch (PH 0) or split in two (PH 1: forward and loss,
@@ -611,12 +655,14 @@ __global__ void __launch_bounds__(256, (PH == 1 ? 4 : 1)) k_fused(KGrid g, KRays
                                            fr.mark_last, fr.mark_overflow);
         if (loss && PH != 2) {
             double lv[1] = {lval};
-            seg_sum_atomic<1>(f, valid, lv, loss);
+            if (!GRID && POSE && PH == 0 && !persistent) frame_sum<1>(f, valid, lv, loss);
+            else seg_sum_atomic<1>(f, valid, lv, loss);
         }
         if (POSE && PH != 1) {
             double six[6] = {0, 0, 0, 0, 0, 0};
             if (valid) pose_six<VIEW>(ray, pa, six);
-            seg_sum_atomic<6>(f, valid, six, grad_pose);
+            if (!GRID && PH == 0 && !persistent) frame_sum<6>(f, valid, six, grad_pose);
+            else seg_sum_atomic<6>(f, valid, six, grad_pose);
         }
         if (stats && PH != 2) {
             long long sv[4] = {inr ? fr.occ : 0, inr ? fr.occ_corners : 0,
@@ -682,7 +728,17 @@ hipError_t launch_backward(const KGrid& g, const KRays& rs, const KOpts& op, con
                            const float* g_depth, float* grad_data, double* grad_pose,
                            hipStream_t st) {
     if (!((grad_data != nullptr) ^ (grad_pose != nullptr))) return hipErrorInvalidValue;
-    // the pose gradient has no one-lane form of its own: a team of one is faster
+    if (grad_pose && rs.n > POSE_BACKWARD_ONE) {
+        by_degree(g.deg, [&](auto D) {
+            constexpr int DEG = decltype(D)::value;
+            auto go = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(blocks_for(rs.n, WAVE)), dim3(WAVE), 0, st, g, rs, op, rgb, depth, nsamp, g_rgb,
+                                   g_depth, grad_pose);
+            };
+            (op.flags & 1) ? go(k_backward_pose<true, DEG>) : go(k_backward_pose<false, DEG>);
+        });
+        return hipGetLastError();
+    }
     const int lt = team_lanes_log2(rs.n, grad_data ? 1 : 2);
     if (lt > 0 || grad_pose)
         return team_backward(g, rs, op, lt, rgb, depth, nsamp, g_rgb, g_depth, grad_data, grad_pose, st);
@@ -768,6 +824,24 @@ static void fused_go(int64_t tiles, dim3 block, hipStream_t st, const KGrid& g, 
     }
 }
 
+// The pose alone of many rays: one lane per ray in two marches, the second of which
+// visits the lit samples only, against a team in one march, whose sums take more
+// registers (the view term spills 55).  us, this form and the better team:
+//   dense maps: the first march ends at a sample's densities (32^3 map: 160,000 rays 289
+//     and 256, 300,000 367 and 440, 816,000 678 and 1044);
+//   with the view term (256^3 room: 160,000 sparse rays 852 and 757, 300,000 1172 and
+//     1406, 600,000 1572 and 1978; frames of 172,800 527 and 527, of 816,000 917 and 1225);
+//   SH degrees 0 and 1, whose records are cheap to read twice (degree 0: 160,000
+//     sparse rays 595 and 433, 300,000 732 and 797, 600,000 908 and 1117; a frame of
+//     816,000 546 and 679);
+//   degree 2 on sparse maps stays with the teams (300,000 1074 and 951, 600,000 1474
+//     and 1343, a frame of 816,000 859 and 810).
+static bool one_lane_pose(const KGrid& g, const KOpts& op, int64_t n_rays, int want) {
+    if ((want & 3) != 2) return false;
+    if (g.probe || (op.flags & 1)) return n_rays > 200000;
+    return g.deg < 2 && n_rays > 250000;
+}
+
 hipError_t launch_fused(const KGrid& g, const KRays& rs, const KOpts& op, const float* tgt_rgb,
                         const float* tgt_depth, const float* frame_weight, int want, float* rgb,
                         float* depth, double* loss, float* grad_data, double* grad_pose,
@@ -777,14 +851,7 @@ hipError_t launch_fused(const KGrid& g, const KRays& rs, const KOpts& op, const 
     // for the pose alone also of one lane, which needs one march only); the counters and the fixed-point
     // scatter, whose result does not depend on the launch form, stay with one
     const int lt = team_lanes_log2(rs.n, want);
-    // The pose alone, many rays, on a dense map: one lane per ray in two marches
-    // reads less than a team in one, as its first march ends at a sample's
-    // densities and its second visits only the lit ones (32^3 map, us: 12 frames
-    // of 16k rays 387 against 360 with teams of two, of 20k 417 and 424, of 30k 480
-    // and 543, of 50k 632 and 834).  On sparse maps the densities are read with the
-    // rest, and the team wins at every size (256^3 room: 12 frames of 30k 1100 and
-    // 988, of 50k 1400 and 1332).
-    const bool alone = (want & 3) == 2 && g.probe && rs.n > 200000;
+    const bool alone = one_lane_pose(g, op, rs.n, want);
     if (variant == 0 && !alone && !gfix && !(want & 4) && (lt > 0 || (want & 3) == 2))
         return team_fused(g, rs, op, lt, tgt_rgb, tgt_depth, frame_weight, want, rgb, depth, loss, grad_data, grad_pose, st);
     // a wave works alone: workgroups of one wave leave no registers and LDS with

@@ -72,7 +72,7 @@ static_assert(GRID_WINDOWS * 5 <= MARK_WORDS, "the kept samples fit in the work-
 // a CU's registers until the slowest of them ends (pose gradient of the
 // 816,000-ray room frame 843 us with eight, 727 with four, 715 with two), two
 // send twice the atomics (2000 rays, Gauss-Newton: 41 us with two, 31 with four).
-constexpr int TEAM_WAVES = 4;
+constexpr int TEAM_WAVES = SUM_WAVES;
 
 struct Team {
     int T;                      // lanes per ray
@@ -114,42 +114,6 @@ __device__ __forceinline__ double team_last(double v, const Team& tm) {
 
 __device__ __forceinline__ double team_sum(double v, const Team& tm) {
     return team_last(team_scan(v, tm), tm);
-}
-
-// Sums over the rays of each frame, added into out[frame * N + n]: one value
-// set per lane with `active`, keyed by frame.  The waves of a workgroup that
-// hold one frame each (rays are grouped by frame) meet in LDS, so a frame
-// receives one atomic per value and workgroup: atomics on one address are
-// served one after another, 70 ns each, and a wave of 64 lanes per ray holds
-// a single ray.  Must be reached by every thread of the workgroup.
-template <int N>
-__device__ __forceinline__ void frame_sum(int key, bool active, const double* vals, double* out) {
-    __shared__ double s_val[TEAM_WAVES][N];
-    __shared__ int s_key[TEAM_WAVES];
-    const int w = threadIdx.x / WAVE, waves = blockDim.x / WAVE;
-    const unsigned long long any = __ballot(active);
-    const int k0 = any ? __builtin_amdgcn_readlane(key, __ffsll((long long)any) - 1) : -1;
-    const bool one = __ballot(active && key != k0) == 0;
-    if (one) {
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-            const double s = wave_sum(active ? vals[n] : 0.0);
-            if (lane_id() == 0) s_val[w][n] = s;
-        }
-    } else {
-        seg_sum_atomic<N>(key, active, vals, out);
-    }
-    if (lane_id() == 0) s_key[w] = one ? k0 : -1;
-    __syncthreads();
-    if (threadIdx.x < N) {
-        for (int i = 0; i < waves; ++i) {
-            const int k = s_key[i];
-            if (k < 0) continue;
-            double s = s_val[i][threadIdx.x];
-            while (i + 1 < waves && s_key[i + 1] == k) s += s_val[++i][threadIdx.x];
-            atomicAdd(out + (int64_t)k * N + threadIdx.x, s);
-        }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -738,10 +702,10 @@ static void team_deg(const KGrid& g, const KRays& rs, const KOpts& op, int log_t
 //               163,200 rays  -787 | 1002 781 834
 //               816,000 rays -1419 | 1914 2061
 // Two lanes for the pose alone stay ahead up to 400,000 rays (PAIRS), with four
-// or more lanes' limit as before; fused pose step and backward of the pose, us,
-// one lane and two: a frame of 360,150 rays of the 256^3 room 964 -> 851 and 756
-// -> 591, 12 sparse frames of 30k 1111 -> 988 and 841 -> 720, of the 32^3 map 465
-// -> 398 (backward); a frame of 576,000 989 -> 1071 and 703 -> 712.
+// or more lanes' limit as before; fused pose step, us, one lane and two: a frame of
+// 360,150 rays of the 256^3 room 964 -> 851, 12 sparse frames of 30k 1111 -> 988; a
+// frame of 576,000 989 -> 1071.  (Larger batches leave the teams: launch_backward,
+// one_lane_pose.)
 // The one-lane kernels stay where they are faster: forward and grid gradients of
 // large batches, which this returns 0 for.
 int team_lanes_log2(int64_t n_rays, int want) {
