@@ -379,7 +379,7 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
         constexpr bool POSE_HERE = POSE && (GAUSS_NEWTON ? SECOND : !SECOND);
         OccCache oc;
         occ_cache_init(oc);
-        bool on = o < lim;
+        bool on = o < lim, dark = true;
         while (__ballot(on)) {
             const int64_t oo = o + tm.sub;
             int64_t nxt = oo + 1;
@@ -406,8 +406,14 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
                 bool have = false;
                 if (work) {
                     have = load_links(g, s.base, idx) > 0;
-                    if (have && g.probe) have = gather_density<DEG>(g, idx, s.f) > 0.f;
-                    if (have) gather_interp<POSE_HERE, POSE_HERE && VIEW, DEG>(g, idx, Y, GY, s.f, v);
+                    if (have && g.probe && __ballot(dark)) {
+                        have = gather_density<DEG>(g, idx, s.f) > 0.f;
+                        dark = !have;
+                    }
+                    if (have) {
+                        gather_interp<POSE_HERE, POSE_HERE && VIEW, DEG>(g, idx, Y, GY, s.f, v);
+                        dark = !(v.sig > 0.f);
+                    }
                 }
                 Lit q;
                 composite<ONE_MARCH || SECOND || BACKWARD, !BACKWARD && !SECOND>(op, tm, have, v.sig, v.s, s.t, cy, q,
