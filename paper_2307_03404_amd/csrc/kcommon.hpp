@@ -536,8 +536,9 @@ __device__ __forceinline__ void load_record(const float* __restrict__ data, int 
 // Raw density of one sample alone, the same value as gather_interp's: eight
 // loads at once, where the records come corner by corner.  Where KGrid::probe is
 // set a march reads it first and leaves a sample without light at that, unless the
-// last sample of every lane at work had light: inside a lit medium the extra read
-// decides nothing.
+// last LIT_RUN samples of every lane at work had light (with one lane per ray; for
+// Gauss-Newton, which has teams at every size, the last): inside a lit medium the
+// extra read decides nothing.
 //
 // It is set for maps that allocate more than half of their lattice: those keep
 // their empty space as records of density zero, which the occupancy bitfield
@@ -547,8 +548,11 @@ __device__ __forceinline__ void load_record(const float* __restrict__ data, int 
 // 98 % of the samples with a record have light, and the extra round trip would
 // cost: view 353 -> 390 us, pose gradient 704 -> 752.  A thin fog in every cell of
 // the 32^3 map, 300,000 rays: view 789 us without the read, 760 with it at every
-// sample, 671 by this rule (SH degree 0: 235, 296, 242; persistent pose step 965,
-// 1072, 992).
+// sample, 664 by this rule (SH degree 0: 235, 293, 237; persistent pose step 965,
+// 1065, 985).  A run of one sample costs the spheres 4 % (pose gradient of a whole
+// frame 637 -> 666 us), runs of 4, 8 and 16 nothing; the fog 664, 671 and 686.
+constexpr int LIT_RUN = 4;
+
 template <int DEG>
 __device__ __forceinline__ float gather_density(const KGrid& g, const int idx[8], const float f[3]) {
     float d[8];

@@ -63,7 +63,7 @@ __device__ __forceinline__ void ray_forward(const KGrid& g, const KOpts& op, con
         int64_t k = ray.k_first;
         OccCache oc;
         occ_cache_init(oc);
-        bool dark = true;
+        int lit_run = 0;                // samples with light since the last one without
         while (n < op.max_samples) {
             Sample s;
             if (!sample_at(g, ray, k, s)) break;
@@ -92,15 +92,18 @@ __device__ __forceinline__ void ray_forward(const KGrid& g, const KOpts& op, con
             if (na == 0) continue;
             ++occ;
             occc += na;
-            if (g.probe && __ballot(dark) && !(gather_density<DEG>(g, idx, s.f) > 0.f)) {
-                dark = true;
+            if (g.probe && __ballot(lit_run < LIT_RUN) && !(gather_density<DEG>(g, idx, s.f) > 0.f)) {
+                lit_run = 0;
                 continue;
             }
             Interp v;
             gather_interp<false, false, DEG>(g, idx, Y, nullptr, s.f, v);
             const float sr = v.sig, s0 = v.s[0], s1 = v.s[1], s2 = v.s[2];
-            dark = !(sr > 0.f);
-            if (dark) continue;
+            if (!(sr > 0.f)) {
+                lit_run = 0;
+                continue;
+            }
+            ++lit_run;
             gradc += na;
             if (marks) {
                 const int64_t o = k - 1 - ray.k_first;
@@ -146,7 +149,7 @@ struct BwdState {
     double AD;          // sum_{j<=i} t_j w_j
     float T;            // T_i
     double L;           // sum_{j<i} sigma_j delta
-    bool dark;          // the last sample had no light: read the next one's density first
+    int lit_run;        // samples with light since the last one without
 };
 
 // Backward work of one occupied sample (Eq. 6-14): updates the running state
@@ -161,15 +164,15 @@ __device__ __forceinline__ bool backward_sample(const KGrid& g, const KOpts& op,
                                                 PoseAcc& pa, int idx[8], float w[8], float& gsig,
                                                 float gs[3]) {
     if (load_links(g, s.base, idx) == 0) return false;
-    if (PROBE && g.probe && __ballot(st.dark) && !(gather_density<DEG>(g, idx, s.f) > 0.f)) {
-        st.dark = true;
+    if (PROBE && g.probe && __ballot(st.lit_run < LIT_RUN) && !(gather_density<DEG>(g, idx, s.f) > 0.f)) {
+        st.lit_run = 0;
         return false;
     }
     Interp v;
     gather_interp<POSE, POSE && VIEW, DEG>(g, idx, Y, GY, s.f, v);
     trilinear_weights(s.f, w);
     const float sr = v.sig;
-    if (PROBE) st.dark = !(sr > 0.f);
+    if (PROBE) st.lit_run = sr > 0.f ? st.lit_run + 1 : 0;
     if (!(sr > 0.f)) return false;      // sigma = 0: no light, zero gradient (ReLU)
     const float delta = op.step_vox;
     const float x = sr * delta;
@@ -310,7 +313,7 @@ __device__ __forceinline__ void ray_backward(const KGrid& g, const KOpts& op, co
                                              int mark_last = 0, bool mark_overflow = true) {
     float GY[9][3];
     if (VIEW) sh9_grad(ray.d[0], ray.d[1], ray.d[2], GY);
-    BwdState st = {{0.0, 0.0, 0.0}, 0.0, 1.f, 0.0, true};
+    BwdState st = {{0.0, 0.0, 0.0}, 0.0, 1.f, 0.0, 0};
     const int64_t ks = ray.k_first, ke = ray.k_first + (n > 0 ? n : 0);
     bool has = n > 0;
     StepRule rule;

@@ -379,7 +379,7 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
         constexpr bool POSE_HERE = POSE && (GAUSS_NEWTON ? SECOND : !SECOND);
         OccCache oc;
         occ_cache_init(oc);
-        bool on = o < lim, dark = true;
+        bool on = o < lim, dark = true;                     // dark: this lane's last sample had no light (Gauss-Newton)
         while (__ballot(on)) {
             const int64_t oo = o + tm.sub;
             int64_t nxt = oo + 1;
@@ -406,14 +406,9 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
                 bool have = false;
                 if (work) {
                     have = load_links(g, s.base, idx) > 0;
-                    if (have && g.probe && __ballot(dark)) {
-                        have = gather_density<DEG>(g, idx, s.f) > 0.f;
-                        dark = !have;
-                    }
-                    if (have) {
-                        gather_interp<POSE_HERE, POSE_HERE && VIEW, DEG>(g, idx, Y, GY, s.f, v);
-                        dark = !(v.sig > 0.f);
-                    }
+                    if (have && g.probe && (!GAUSS_NEWTON || __ballot(dark))) have = gather_density<DEG>(g, idx, s.f) > 0.f;
+                    if (have) gather_interp<POSE_HERE, POSE_HERE && VIEW, DEG>(g, idx, Y, GY, s.f, v);
+                    if (GAUSS_NEWTON) dark = !(have && v.sig > 0.f);
                 }
                 Lit q;
                 composite<ONE_MARCH || SECOND || BACKWARD, !BACKWARD && !SECOND>(op, tm, have, v.sig, v.s, s.t, cy, q,
@@ -556,8 +551,8 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
     }
     if (KEEP) {
         cy = Carry{0.0, {0.0, 0.0, 0.0}, 0.0, 1.f};
-        for (int b = 0; __ballot(b < windows); ++b) {
-            const int32_t at = b < windows ? keep_at[b * WAVE] : -1;
+        for (int b = 0; GRID ? b < windows : __ballot(b < windows) != 0; ++b) {
+            const int32_t at = GRID || b < windows ? keep_at[b * WAVE] : -1;
             const bool have = valid && at >= 0;
             Sample s;
             s.t = 0.f;
@@ -592,7 +587,8 @@ __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWA
                 scatter_merged<DEG>(q.lit, s.base, idx, w, gsig, gs, Y, wc, io.grad);
             }
         }
-        if (__ballot(spilled)) march(std::integral_constant<bool, true>{}, resume, valid && spilled ? kept : 0);
+        if (GRID ? spilled : __ballot(spilled) != 0)
+            march(std::integral_constant<bool, true>{}, resume, valid && spilled ? kept : 0);
     }
     if (POSE && !GAUSS_NEWTON) {
         if (ONE_MARCH) {
