@@ -841,9 +841,11 @@ static void fused_go(int64_t tiles, dim3 block, hipStream_t st, const KGrid& g, 
 // visits the lit samples only, against a team in one march, whose sums take more
 // registers (the view term spills 55).  us, this form and the better team:
 //   dense maps: the first march ends at a sample's densities (32^3 map: 160,000 rays 289
-//     and 256, 300,000 367 and 440, 816,000 678 and 1044);
+//     and 256, 300,000 367 and 440, 816,000 678 and 1044; with the view term 64,000
+//     317 and 195, 120,000 331 and 336, 160,000 318 and 367);
 //   with the view term (256^3 room: 160,000 sparse rays 852 and 757, 300,000 1172 and
-//     1406, 600,000 1572 and 1978; frames of 172,800 527 and 527, of 816,000 917 and 1225);
+//     1406, 600,000 1572 and 1978; frames of 172,800 527 and 527, of 816,000 917 and 1225;
+//     frames in raster order, 120,000 rays 473 and 549, 156,400 566 and 641);
 //   SH degrees 0 and 1, whose records are cheap to read twice (degree 0: 160,000
 //     sparse rays 595 and 433, 300,000 732 and 797, 600,000 908 and 1117; a frame of
 //     816,000 546 and 679);
@@ -851,8 +853,8 @@ static void fused_go(int64_t tiles, dim3 block, hipStream_t st, const KGrid& g, 
 //     and 1343, a frame of 816,000 859 and 810).
 static bool one_lane_pose(const KGrid& g, const KOpts& op, int64_t n_rays, int want) {
     if ((want & 3) != 2) return false;
-    if (g.probe || (op.flags & 1)) return n_rays > 200000;
-    return g.deg < 2 && n_rays > 250000;
+    if (op.flags & 1) return n_rays > (g.probe ? 120000 : 150000);
+    return g.probe ? n_rays > 200000 : g.deg < 2 && n_rays > 250000;
 }
 
 hipError_t launch_fused(const KGrid& g, const KRays& rs, const KOpts& op, const float* tgt_rgb,

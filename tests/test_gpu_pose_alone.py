@@ -55,9 +55,9 @@ def _check(wl, fused, backward):
 
 
 @pytest.mark.parametrize("scene,n,deg,view", [
-    ("room", 200000, 2, True), ("room", 200001, 2, True), ("ball", 200000, 2, True), ("ball", 200001, 2, True),
-    ("room", 250000, 0, False), ("room", 250001, 0, False), ("room", 250001, 1, False), ("room", 200001, 1, True),
-    ("ball", 200001, 1, False), ("ball", 200001, 0, True),
+    ("room", 150000, 2, True), ("room", 150001, 2, True), ("ball", 120000, 2, True), ("ball", 120001, 2, True),
+    ("room", 250000, 0, False), ("room", 250001, 0, False), ("room", 250001, 1, False), ("room", 150001, 1, True),
+    ("ball", 200001, 1, False), ("ball", 120001, 0, True),
     ("room", 400000, 2, False), ("room", 400001, 2, False)])
 def test_fused(scene, n, deg, view):
     _check(_workload(scene, n, deg, view), True, False)
