@@ -56,7 +56,7 @@
 extern "C" {
 #endif
 
-#define PXM_ABI_VERSION 7   /* 7: pxm_tv_grad_set; 6: SH degree 0/1 records (pxm_grid.sh_degree) */
+#define PXM_ABI_VERSION 7   /* 7: pxm_tv_grad_set (since then only pxm_gather_rays was added); 6: SH degree 0/1 records (pxm_grid.sh_degree) */
 #define PXM_RECORD 28          /* floats per vertex at SH degree 2: density + 3 x 9 SH */
 #define PXM_RECORD_FLOATS(d) ((d) == 0 ? 4 : (d) == 1 ? 16 : 28)   /* per SH degree */
 
@@ -425,9 +425,10 @@ size_t pxm_workspace_bytes(const pxm_grid *grid, const pxm_rays *rays, const pxm
  * Launch tuning for pxm_render_fused (process-wide; read at each call):
  *   block    rays per workgroup of variants 1 and 2 (64, 128 or 256; 0 =
  *            default 256)
- *   variant  0 = plain launches: one wave per tile of 64 rays, and for the pose
- *            alone, or where a batch is too small to fill the card with one
- *            lane per ray, a team of lanes per ray,
+ *   variant  0 = plain launches: one wave per tile of 64 rays, or a team of
+ *            lanes per ray where a batch is too small to fill the card with
+ *            one lane each (and, for the pose alone at SH degree 2 without the
+ *            view-direction term on a sparse map, at every size),
  *            1 = persistent workgroups
  *            pulling ray tiles from a device counter in the workspace,
  *            2 = two persistent launches: the forward and loss (few

@@ -486,7 +486,7 @@ __device__ __forceinline__ void backward_ray(const KGrid& g, const KRays& rs, co
 }
 
 // It keeps no work masks, so its LDS (the staging alone) holds 13 waves on a CU,
-// and its 168 registers 3 on a SIMD.  With the mask region allocated, and so 2,
+// and its 137 registers (of 168 there) 3 on a SIMD.  With the mask region allocated, and so 2,
 // the backward of a 1200 x 680 frame of the 256^3 room took 827 us and takes 762,
 // of 8 frames of the 512^3 room 14.2 and 11.7 ms, of a frame of the 32^3 map 467
 // and 372 us.

@@ -24,12 +24,12 @@
 //
 // Gauss-Newton composites first, each team keeping the positions of its lit windows, then
 // gathers those again with their spatial derivatives and sums its Jacobian rows
-// in FP32 in sample order, lane after lane: the solve of a badly conditioned
-// frame multiplies their rounding, and its path is then the same at every team
-// width.
+// in FP32 in sample order, lane after lane, as one lane per ray would: the solve of a
+// badly conditioned frame multiplies their rounding.  Prefixes and frame sums are
+// FP64 sums that the team's width groups, so the last bits may differ between widths.
 //
 // Grid gradient: the march keeps (density, three colour pre-activations) of
-// its lit samples in LDS, STORE_WINDOWS windows of them, so that the backward
+// its lit samples in LDS, GRID_WINDOWS windows of them, so that the backward
 // pass needs only their links again; a ray with more is marched and gathered
 // again from the first window that did not fit.  The scatter is the shared
 // wave-wide merge.
@@ -292,9 +292,11 @@ __device__ __forceinline__ void jacobian_window(const KGrid& g, const KOpts& op,
 // words, links, then the records of eight corners one after another) at the
 // waves the registers allow: 4 on a SIMD forward, 3 with the grid gradient, 2
 // with the pose sums (60 registers of FP64).  With both gradients the limit of 2
-// costs a few spilled registers and is worth them: 4096 rays 89 -> 58 us, 83,583
-// rays 832 -> 570 us (a limit of 3 on the pose kernels spills 90 registers and
-// takes four times as long).
+// costs 16 spilled registers at SH degree 2 and is worth them: 4096 rays 89 -> 58 us,
+// 83,583 rays 832 -> 570 us (a limit of 3 on the pose kernels spills 90 registers and
+// takes four times as long).  The view term spills 55 for the pose alone and 61 with
+// both (32 and 42 at degree 0): batches above 120,000 to 150,000 rays leave the team
+// for it (one_lane_pose).
 template <int MODE, bool GRID, bool POSE, bool VIEW, int DEG>
 __global__ void __launch_bounds__(WAVE * TEAM_WAVES, POSE && MODE != TEAM_BACKWARD ? 2 : 1) k_team(KGrid g, KRays rs, KOpts op, int log_t, TeamIO io) {
     constexpr bool BACKWARD = MODE == TEAM_BACKWARD;
