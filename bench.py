@@ -93,16 +93,19 @@ def measured_traffic(workload_name, block, variant):
         return None
     try:
         with open(os.path.join(PROFILES_DIR, TRAFFIC_PROFILES[workload_name])) as fh:
-            kv = dict(m.groups() for m in re.finditer(r"^- (\w+): `([^`]*)`", fh.read(), re.M))
-        if (kv.get("sources_sha256") != sources_sha256() or kv.get("workload") != workload_name
-                or int(kv.get("block", -1)) != block or int(kv.get("variant", -1)) != variant):
-            return None
-        return {"bytes": float(kv["traffic_bytes_per_launch"]),
-                "read_bytes": float(kv["fetch_kib_per_launch"]) / float(kv["fetch_scale"]) * 1024.0,
-                "write_bytes": float(kv["write_kib_per_launch"]) / float(kv["write_scale"]) * 1024.0,
-                "kernel_us_profiled": float(kv["kernel_us"]) if "kernel_us" in kv else None}
+            shapes = re.split(r"^(?=- workload: )", fh.read(), flags=re.M)
+        for text in shapes:
+            kv = dict(m.groups() for m in re.finditer(r"^- (\w+): `([^`]*)`", text, re.M))
+            if (kv.get("sources_sha256") != sources_sha256() or kv.get("workload") != workload_name
+                    or int(kv.get("block", -1)) != block or int(kv.get("variant", -1)) != variant):
+                continue
+            return {"bytes": float(kv["traffic_bytes_per_launch"]),
+                    "read_bytes": float(kv["fetch_kib_per_launch"]) / float(kv["fetch_scale"]) * 1024.0,
+                    "write_bytes": float(kv["write_kib_per_launch"]) / float(kv["write_scale"]) * 1024.0,
+                    "kernel_us_profiled": float(kv["kernel_us"]) if "kernel_us" in kv else None}
     except (OSError, KeyError, ValueError):
-        return None
+        pass
+    return None
 
 
 def roofline(bytes_alg, bytes_min, kern_ms, traffic, kernel, workload_name):
