@@ -384,7 +384,7 @@ struct Records {
 // tenth of a sparse map's).  Then a group of 8 lanes takes a listed vertex: lane
 // p < S/4 (7 at SH degree 2) fetches float4 p of the 8 corner records and writes
 // float4 p of each allocated fine record.
-// 256^3 room to 511^3, 19.9 M records of 112 bytes: 1015 us (listing 200), of
+// 256^3 room to 511^3, 20.3 M records of 112 bytes: 1048 us (listing 200), of
 // which the writes alone, filled in order, would take 408; 8 lanes for every
 // coarse vertex, with branches around each corner and record, took 1446.
 // Requesting the next vertex's records early, two z-neighbours' records in one
