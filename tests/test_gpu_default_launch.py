@@ -91,6 +91,11 @@ def test_loss_alone_and_grid_alone(n, deg):
     wl, ref = reference(wl.replace(grid=synth.with_sh_degree(wl.grid, deg)))
     _fused(wl, ref, 0)
     _fused(wl, ref, 1)
+    pxm = _pxm()
+    rgb, depth, ns = pxm.render_forward(pxm.grid_to_device(wl.grid), pxm.rays_to_device(wl.rays), wl.opts)
+    assert_r28(_host(rgb), ref["rgb"], TAU_FWD, "forward rgb")
+    assert_r28(_host(depth), ref["depth"], TAU_FWD, "forward depth")
+    assert np.mean(_host(ns) != ref["nsamp"]) <= 1e-3
 
 
 @functools.lru_cache(maxsize=1)
